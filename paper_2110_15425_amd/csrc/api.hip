@@ -529,8 +529,8 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
   const size_t rec_bytes = 4u * (cm::rec_words(B) + (tc.every ? cm::tc_words(a.tc_k) : 0u));
   // the lane kernel also stages its drain through LDS after the window
   const size_t stage = scan ? 0 : cm::lane_stage_bytes((int)m->kind, (int)m->precision, block);
-  const uint64_t wmax =
-      std::min<size_t>(kLdsBudget, h->lds_per_block > stage ? h->lds_per_block - stage : 0) / rec_bytes;
+  const size_t lds_max = h->lds_per_block - (m->precision == CM_FP64 ? cm::kNormTabBytes : 0);
+  const uint64_t wmax = std::min<size_t>(kLdsBudget, lds_max > stage ? lds_max - stage : 0) / rec_bytes;
   bool direct = false;
   // settings touched by one chunk: at most floor((chunk-1)/T) + 2
   if (wmax < 2 || (chunk - 1) / T + 2 > wmax) {
@@ -544,7 +544,7 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
   groups = (runs + chunk - 1) / chunk;
   lds = direct ? 0 : (size_t)a.window * rec_bytes;
   lds += stage;
-  if (lds > h->lds_per_block) return fail(CM_E_UNSUPPORTED, "lane kernel: LDS stage too large for this block size");
+  if (lds > lds_max) return fail(CM_E_UNSUPPORTED, "lane kernel: LDS stage too large for this block size");
   return ok();
 }
 

@@ -19,6 +19,10 @@ __host__ __device__ inline uint32_t rec_words(uint32_t n_bins) { return 2u * n_b
 constexpr uint32_t kTcWords = 6;
 __host__ __device__ inline uint32_t tc_words(uint32_t k) { return 2u * kTcWords * k; }
 
+// LDS the double-precision kernels hold beside what a launch asks for: the
+// normals' table (normal64.hpp).
+constexpr size_t kNormTabBytes = 4096;
+
 // Arguments of the lane-per-run simulation kernels (DDM, conflict LCA).
 struct SimArgs {
   uint64_t trials, n_settings, total_runs, seed;

@@ -37,6 +37,7 @@
 
 #include "internal.hpp"
 #include "lca_step.hpp"
+#include "normal64.hpp"
 #include "rng.hpp"
 
 namespace cm {
@@ -107,8 +108,8 @@ __device__ __forceinline__ void lca_update(const LoopArgs& a, double x0, double 
                                            double in1, float idt0, float idt1, double z0, double z1,
                                            float zf0, float zf1, double& y0, double& y1) {
   if (PREC == CM_FP64) {
-    y0 = (x0 + (((in0 - a.leak * x0) - a.comp * x1) * a.dt)) + a.b * z0;
-    y1 = (x1 + (((in1 - a.leak * x1) - a.comp * x0) * a.dt)) + a.b * z1;
+    y0 = lca_next_f64(x0, x1, in0, a.leak, a.comp, a.dt, a.b, z0);
+    y1 = lca_next_f64(x1, x0, in1, a.leak, a.comp, a.dt, a.b, z1);
   } else {
     const LcaF32 pf = lca_f32(a.leak, a.comp, a.dt, a.b);
     const float xf0 = (float)x0, xf1 = (float)x1;
@@ -125,10 +126,10 @@ __device__ __forceinline__ void lca_update(const LoopArgs& a, double x0, double 
 template <int PREC>
 __device__ __forceinline__ void lca_step(const LoopArgs& a, double x0, double x1, double in0,
                                          double in1, float idt0, float idt1, const Words& w,
-                                         double& y0, double& y1) {
+                                         const NormTab* nt, double& y0, double& y1) {
   double z0 = 0.0, z1 = 0.0;
   float zf0 = 0.0f, zf1 = 0.0f;
-  if (PREC == CM_FP64) normals64(w, z0, z1);
+  if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
   else normals32(w, zf0, zf1);
   lca_update<PREC>(a, x0, x1, in0, in1, idt0, idt1, z0, z1, zf0, zf1, y0, y1);
 }
@@ -247,6 +248,10 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
   // reached uniformly.
   __shared__ double fold_v[2][kLoopBlock / 64], fold_s[2][kLoopBlock / 64];
   __shared__ uint32_t fold_j[2][kLoopBlock / 64];
+  __shared__ NormLds<PREC> norm;
+  norm.load();
+  __syncthreads();
+  const NormTab* nt = norm.get();
   uint32_t folds = 0;
   const uint32_t j0 = P > 64 ? threadIdx.x : (threadIdx.x & 63u) % (uint32_t)P;
   const uint32_t teams_per_block = kLoopBlock / P;
@@ -281,7 +286,7 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
       if constexpr (P == 64) {
         if ((k & 63u) == 0u) {
           const Words w = philox(k + lane, t, s, 0u, k0, k1);
-          if (PREC == CM_FP64) normals64(w, ez0, ez1);
+          if (PREC == CM_FP64) normals64(w, *nt, ez0, ez1);
           else normals32(w, ef0, ef1);
         }
       }
@@ -317,10 +322,10 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
             const Words w = philox_stream(sk, kStreamLook | (ju[u] * M + m), k0, k1);
             double y0, y1;
             if constexpr (P == 64)
-              lca_step<PREC>(a, x0, x1, i0[u], i1[u], f0[u], f1[u], w, y0, y1);
+              lca_step<PREC>(a, x0, x1, i0[u], i1[u], f0[u], f1[u], w, nt, y0, y1);
             else
               lca_step<PREC>(a, x0, x1, i0[u], i1[u], (float)(i0[u] * a.dt), (float)(i1[u] * a.dt), w,
-                             y0, y1);
+                             nt, y0, y1);
             gs[u] = gs[u] + ((c ? y1 - y0 : y0 - y1) - dx);
           }
         }
@@ -437,7 +442,7 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
         }
         lca_update<PREC>(a, x0, x1, e0, e1, g0, g1, z0, z1, zf0, zf1, y0, y1);
       } else {
-        lca_step<PREC>(a, x0, x1, e0, e1, g0, g1, philox(k, t, s, 0u, k0, k1), y0, y1);
+        lca_step<PREC>(a, x0, x1, e0, e1, g0, g1, philox(k, t, s, 0u, k0, k1), nt, y0, y1);
       }
       x0 = y0;
       x1 = y1;

@@ -109,30 +109,6 @@ __device__ __forceinline__ Words philox_run(uint32_t n, uint64_t kM, const RunKe
   return Words{c0, c1, c2, c3};
 }
 
-// 53-bit uniform in (0, 1] from a word pair: ((hi:lo) >> 11) + 1, times 2^-53.
-// Built from two exact int->double conversions (the value fits in 53 bits).
-__device__ __forceinline__ double uniform53(uint32_t lo, uint32_t hi) {
-  const uint32_t top = hi >> 11;                   // bits 52..32 of the 53-bit value
-  const uint32_t bot = (hi << 21) | (lo >> 11);    // bits 31..0
-  const double v = __dadd_rn(__dmul_rn((double)top, 4294967296.0), (double)bot);
-  return __dmul_rn(__dadd_rn(v, 1.0), 0x1p-53);
-}
-
-// Two standard normals (Box-Muller) from one block, in double:
-// rho = sqrt(-2 ln u_a), angle 2 pi u_b.  The angle is evaluated as
-// sincospi(2 u_b): 2 u_b is exact, so the argument reduction is a trivial
-// exact one instead of a general Payne-Hanek reduction, and the result is
-// cos/sin of 2 pi u_b without the rounding of the product 2 pi u_b.
-__device__ __forceinline__ void normals64(const Words& w, double& z0, double& z1) {
-  const double ua = uniform53(w.w0, w.w1);
-  const double ub = uniform53(w.w2, w.w3);
-  const double rho = sqrt(__dmul_rn(-2.0, log(ua)));
-  double s, c;
-  sincospi(__dmul_rn(2.0, ub), &s, &c);
-  z0 = __dmul_rn(rho, c);
-  z1 = __dmul_rn(rho, s);
-}
-
 // Two standard normals in float from the top 24 bits of words 1 and 3, on
 // the hardware transcendental units: v_log_f32 is log2, and v_sin_f32 /
 // v_cos_f32 take their argument in revolutions, so the angle 2*pi*u needs no

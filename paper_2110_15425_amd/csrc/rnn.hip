@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "internal.hpp"
+#include "normal64.hpp"
 #include "rng.hpp"
 
 namespace cm {
@@ -274,6 +275,9 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
   __shared__ double rt[NB * 4][64];  // [K block (b, q)][lane]
   __shared__ double ypart[4][2][16];
   __shared__ double Rs[2][NU];
+  __shared__ NormLds<CM_FP64> norm;
+  norm.load();
+  __syncthreads();
   for (int i = tid; i < 2 * NU; i += kRnnBlock) Rs[i / NU][i % NU] = a.R[i];
 
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
         const uint32_t m = (uint32_t)(8 * b + 2 * g + h);
         const Words wd = philox(m, S.t, S.s, kStreamDrive, k0, k1);
         double u0, u1;
-        normals64(wd, u0, u1);
+        normals64(wd, norm.t, u0, u1);
         gu[bw][2 * h] = gd * u0;
         gu[bw][2 * h + 1] = gd * u1;
       }
@@ -360,7 +364,7 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
         const uint32_t m = (uint32_t)(8 * b + 2 * g + h);
         const Words wd = philox(S.n - 1u, S.t, S.s, m, k0, k1);
         double xi[2];
-        normals64(wd, xi[0], xi[1]);
+        normals64(wd, norm.t, xi[0], xi[1]);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const int q = 2 * h + e;

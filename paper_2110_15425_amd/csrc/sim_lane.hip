@@ -24,6 +24,7 @@
 #include "internal.hpp"
 #include "prep_score.hpp"
 #include "lca_step.hpp"
+#include "normal64.hpp"
 #include "rng.hpp"
 
 namespace cm {
@@ -248,6 +249,7 @@ __device__ __forceinline__ uint64_t opaque_s(uint64_t v) {
 // Step n uses element (n-1) & 1 of block (n-1) >> 1.
 template <int PREC>
 struct DDM {
+  static constexpr int kPrec = PREC;
   double x, a_step;
   RunKey rk;
   static constexpr int kWidth = 1;
@@ -266,7 +268,7 @@ struct DDM {
   template <class H>
   __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, double z, float zf,
                                       float af, double guard, const H& hook) {
-    if (PREC == CM_FP64) x = (x + a_step) + A.b * z;
+    if (PREC == CM_FP64) x = __builtin_fma(A.b, z, x + a_step);
     else x = x + (double)fmaf(A.bf, zf, af);
     if constexpr (H::kPerStep) {
       L.n = n;
@@ -288,7 +290,7 @@ struct DDM {
   // that many whole pairs left before the cap.
   template <class H>
   __device__ __forceinline__ bool pairs_loop(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                             uint32_t pairs, const H& hook) {
+                                             uint32_t pairs, const NormTab* nt, const H& hook) {
     const float af = (float)a_step;
     const double guard = A.thresh - 2.0 * A.flag_eps;
     const uint32_t n0 = L.n, b0 = n0 >> 1;  // a running lane enters at an even step count
@@ -297,7 +299,7 @@ struct DDM {
       const Words w = philox_run(b0, opaque_s(kM), rk, k0, k1);
       double z0 = 0, z1 = 0;
       float f0 = 0, f1 = 0;
-      if (PREC == CM_FP64) normals64(w, z0, z1);
+      if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
       else normals32(w, f0, f1);
       const uint32_t n = n0 + 2u * p;
       if (!one(A, L, n + 1u, z0, f0, af, guard, hook)) return false;
@@ -313,14 +315,14 @@ struct DDM {
   // need no cap test; an odd cap leaves one single step.
   template <class H>
   __device__ __forceinline__ bool advance(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                          int pairs, const H& hook) {
+                                          int pairs, const NormTab* nt, const H& hook) {
     const uint32_t t = uniform_trips((uint32_t)pairs, (A.max_steps - L.n) >> 1);
-    if (!pairs_loop(A, L, k0, k1, t, hook)) return false;
+    if (!pairs_loop(A, L, k0, k1, t, nt, hook)) return false;
     if (L.n + 1u == A.max_steps) {  // an odd cap's own step, first of a pair
       const Words w = philox_run(L.n >> 1, 0ull, rk, k0, k1);
       double z0 = 0, z1 = 0;
       float f0 = 0, f1 = 0;
-      if (PREC == CM_FP64) normals64(w, z0, z1);
+      if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
       else normals32(w, f0, f1);
       const uint32_t n = L.n + 1u;
       if (!one(A, L, n, z0, f0, (float)a_step, A.thresh - 2.0 * A.flag_eps, hook)) return false;
@@ -343,7 +345,7 @@ struct DDM {
     rk = run_key(L.t, L.s, k0, k1);
   }
   __device__ __forceinline__ void free_steps(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                             uint32_t steps) {
+                                             uint32_t steps, const NormTab* nt) {
     const float af = (float)a_step;
     const uint32_t b0 = L.n >> 1;
     uint64_t kM = 0;
@@ -352,9 +354,9 @@ struct DDM {
       kM += kPhiloxM0;
       if (PREC == CM_FP64) {
         double z0, z1;
-        normals64(w, z0, z1);
-        x = (x + a_step) + A.b * z0;
-        x = (x + a_step) + A.b * z1;
+        normals64(w, *nt, z0, z1);
+        x = __builtin_fma(A.b, z0, x + a_step);
+        x = __builtin_fma(A.b, z1, x + a_step);
       } else {
         float f0, f1;
         normals32(w, f0, f1);
@@ -380,6 +382,7 @@ template <int PREC>
 struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   double x0, x1;
   RunKey rk;
+  static constexpr int kPrec = PREC;
   static constexpr int kWidth = 2;
 
   __device__ __forceinline__ void begin(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1) {
@@ -403,13 +406,13 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   // (FP32 steps).
   template <class H>
   __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, const Words& w,
-                                      float& xf0, float& xf1, const H& hook) {
+                                      float& xf0, float& xf1, const NormTab* nt, const H& hook) {
     double y0, y1;
     if constexpr (PREC == CM_FP64) {
       double z0, z1;
-      normals64(w, z0, z1);
-      y0 = (x0 + (((this->in0 - A.leak * x0) - A.comp * x1) * A.dt)) + A.b * z0;
-      y1 = (x1 + (((this->in1 - A.leak * x1) - A.comp * x0) * A.dt)) + A.b * z1;
+      normals64(w, *nt, z0, z1);
+      y0 = lca_next_f64(x0, x1, this->in0, A.leak, A.comp, A.dt, A.b, z0);
+      y1 = lca_next_f64(x1, x0, this->in1, A.leak, A.comp, A.dt, A.b, z1);
     } else {
       float z0, z1;
       normals32(w, z0, z1);
@@ -434,7 +437,8 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
     // implies float(x) >= float(guard).
     bool near;
     if constexpr (PREC == CM_FP64) {
-      near = (x0 > x1 ? x0 : x1) >= A.thresh - 2.0 * A.flag_eps;
+      const double guard = A.thresh - 2.0 * A.flag_eps;
+      near = (x0 >= guard) | (x1 >= guard);
     } else {
       xf0 = (float)x0;
       xf1 = (float)x1;
@@ -451,13 +455,13 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   // many left before the cap.
   template <class H>
   __device__ __forceinline__ bool steps_loop(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                             uint32_t steps, const H& hook) {
+                                             uint32_t steps, const NormTab* nt, const H& hook) {
     const uint32_t n0 = L.n;
     float xf0 = (float)x0, xf1 = (float)x1;
     uint64_t kM = 0;
     for (uint32_t k = 0; k < steps; ++k) {
       const Words w = philox_run(n0, opaque_s(kM), rk, k0, k1);
-      if (!one(A, L, n0 + k + 1u, w, xf0, xf1, hook)) return false;
+      if (!one(A, L, n0 + k + 1u, w, xf0, xf1, nt, hook)) return false;
       kM += kPhiloxM0;
     }
     L.n = n0 + steps;
@@ -466,10 +470,10 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
 
   template <class H>
   __device__ __forceinline__ bool advance(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                          int steps, const H& hook) {
+                                          int steps, const NormTab* nt, const H& hook) {
     // the step cap bounds the trip count, so the body needs no cap test
     const uint32_t t = uniform_trips((uint32_t)steps, A.max_steps - L.n);
-    if (!steps_loop(A, L, k0, k1, t, hook)) {
+    if (!steps_loop(A, L, k0, k1, t, nt, hook)) {
       // stopped near the threshold after step L.n: the exact tests
       const double th = A.thresh, eps = A.flag_eps;
       if (near_th(x0, th, eps) || near_th(x1, th, eps)) L.flag = true;
@@ -508,7 +512,7 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
     rk = run_key(L.t, L.s, k0, k1);
   }
   __device__ __forceinline__ void free_steps(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
-                                             uint32_t steps) {
+                                             uint32_t steps, const NormTab* nt) {
     float xf0 = 0.0f, xf1 = 0.0f;
     const uint32_t n0 = L.n;
     uint64_t kM = 0;
@@ -517,9 +521,9 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
       kM += kPhiloxM0;
       if constexpr (PREC == CM_FP64) {
         double z0, z1;
-        normals64(w, z0, z1);
-        const double y0 = (x0 + (((this->in0 - A.leak * x0) - A.comp * x1) * A.dt)) + A.b * z0;
-        const double y1 = (x1 + (((this->in1 - A.leak * x1) - A.comp * x0) * A.dt)) + A.b * z1;
+        normals64(w, *nt, z0, z1);
+        const double y0 = lca_next_f64(x0, x1, this->in0, A.leak, A.comp, A.dt, A.b, z0);
+        const double y1 = lca_next_f64(x1, x0, this->in1, A.leak, A.comp, A.dt, A.b, z1);
         x0 = y0;
         x1 = y1;
       } else {
@@ -552,7 +556,7 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
 // counters.
 template <class M, bool TC, int BLOCK>
 __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32_t* lds, uint32_t& next,
-                                           uint32_t* drain_cnt) {
+                                           uint32_t* drain_cnt, const NormTab* nt) {
   const uint64_t r1 = min(r0 + a.chunk, a.total_runs);
   const uint32_t len = (uint32_t)(r1 - r0);
   const uint32_t s_lo = (uint32_t)(r0 / a.trials);
@@ -604,7 +608,7 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
     // one LDS word, the same for the whole wavefront
     if (__hip_atomic_load(&next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= len) break;
     bool running = have;
-    if (running) running = m.advance(a, L, k0, k1, (int)a.steps_per_sync, hook);
+    if (running) running = m.advance(a, L, k0, k1, (int)a.steps_per_sync, nt, hook);
     if (have && !running) {
       finish();
       off = atomicAdd(&next, 1u);
@@ -655,7 +659,7 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
       }
     }
     bool running = have;
-    if (__any(running)) running = running && m.advance(a, L, k0, k1, kDrainSteps, hook);
+    if (__any(running)) running = running && m.advance(a, L, k0, k1, kDrainSteps, nt, hook);
     if (have && !running) {
       finish();
       have = false;
@@ -670,11 +674,13 @@ void sim_lane_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];  // 8-byte aligned window
   __shared__ uint32_t next;
   __shared__ uint32_t drain_cnt[BLOCK / 64];
+  __shared__ NormLds<M::kPrec> norm;
+  norm.load();  // visible after lane_chunk's first barrier
   uint32_t sw = 0;
   while (sw + 1 < batch.n && blockIdx.x >= batch.base[sw + 1]) ++sw;
   const SimArgs& a = batch.a[sw];
   lane_chunk<M, TC, BLOCK>(a, (uint64_t)(blockIdx.x - batch.base[sw]) * a.chunk, (uint32_t*)lds_u64, next,
-                           drain_cnt);
+                           drain_cnt, norm.get());
 }
 
 // The persistent kernel of the device work queue.
@@ -716,6 +722,8 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
   __shared__ QueueReq batch[kBlock];
   __shared__ double red_d[kBlock / 64];
   __shared__ unsigned long long red_k[kBlock / 64], red_c[kBlock / 64];
+  __shared__ NormLds<M::kPrec> norm;
+  norm.load();
   constexpr uint32_t kItem = 0, kQuit = 1, kPull = 2;
   uint32_t seen_slot = ~0u;  // thread 0: the request whose preparation this workgroup last waited for
   uint64_t seen_target = 0;
@@ -851,7 +859,7 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
     }
     __syncthreads();
     lane_chunk<M, false, kBlock>(desc.a, (uint64_t)(item - desc.pieces) * desc.a.chunk, (uint32_t*)lds_u64,
-                                 next, drain_cnt);
+                                 next, drain_cnt, norm.get());
     __builtin_amdgcn_s_waitcnt(0);  // this wave's flushes are performed
     __syncthreads();                // and every wave's
     if (threadIdx.x == 0) {
@@ -888,6 +896,9 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
 template <int PREC>
 __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];
+  __shared__ NormLds<PREC> norm;
+  norm.load();
+  const NormTab* nt = norm.get();
   uint32_t* lds = (uint32_t*)lds_u64;
   uint32_t sw = 0;
   while (sw + 1 < batch.n && blockIdx.x >= batch.base[sw + 1]) ++sw;
@@ -934,9 +945,9 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
       double d1, d2;
       if (PREC == CM_FP64) {
         double z0, z1;
-        normals64(w, z0, z1);
-        d1 = as + a.b * z0;
-        d2 = as + a.b * z1;
+        normals64(w, *nt, z0, z1);
+        d1 = __builtin_fma(a.b, z0, as);
+        d2 = __builtin_fma(a.b, z1, as);
       } else {
         float z0, z1;
         normals32(w, z0, z1);
@@ -995,6 +1006,9 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
 // rate it reaches is the measured ceiling of the step's instruction mix.
 template <class M>
 __global__ __launch_bounds__(kBlock) void ceiling_kernel(SimArgs a, uint32_t steps, double* out) {
+  __shared__ NormLds<M::kPrec> norm;
+  norm.load();
+  __syncthreads();
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   Lane L{};
   L.s = 0;
@@ -1002,7 +1016,7 @@ __global__ __launch_bounds__(kBlock) void ceiling_kernel(SimArgs a, uint32_t ste
   L.n = 2u * ((uint32_t)g & 255u);  // lanes of a sweep are at different steps
   M m;
   m.free_init(a, L, (uint32_t)a.seed, (uint32_t)(a.seed >> 32));
-  m.free_steps(a, L, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), steps);
+  m.free_steps(a, L, (uint32_t)a.seed, (uint32_t)(a.seed >> 32), steps, norm.get());
   double st[M::kWidth];
   m.state(st);
   out[g] = st[0];

@@ -11,6 +11,7 @@
 // results); only the execution structure differs.
 #include "internal.hpp"
 #include "lca_step.hpp"
+#include "normal64.hpp"
 #include "rng.hpp"
 
 namespace cm {
@@ -59,7 +60,7 @@ __global__ void uf_rng_kernel(UnfusedArgs a, uint32_t n, int cur) {
     const Words w = philox(k, t, s, 0u, k0, k1);
     if (PREC == CM_FP64) {
       double z0, z1;
-      normals64(w, z0, z1);
+      normals64(w, kNormTab, z0, z1);
       if (a.kind == CM_DDM) {
         a.z[2 * (uint64_t)r] = ((n - 1u) & 1u) ? z1 : z0;
       } else {
@@ -93,15 +94,15 @@ __global__ void uf_update_kernel(UnfusedArgs a, int cur) {
     if (a.kind == CM_DDM) {
       const double drift = a.n_signals ? a.grid[(uint64_t)s * a.n_signals] : a.drift;
       const double as = drift * a.dt;
-      if (PREC == CM_FP64) x[0] = (x[0] + as) + a.b * z[0];
+      if (PREC == CM_FP64) x[0] = __builtin_fma(a.b, z[0], x[0] + as);
       else x[0] = x[0] + (double)fmaf((float)a.b, (float)z[0], (float)as);
     } else {
       const uint32_t stim = t % 9u;
       const double* d = a.drive + ((uint64_t)s * 9u + stim) * 2u;
       double y0, y1;
       if (PREC == CM_FP64) {
-        y0 = (x[0] + (((d[0] - a.leak * x[0]) - a.comp * x[1]) * a.dt)) + a.b * z[0];
-        y1 = (x[1] + (((d[1] - a.leak * x[1]) - a.comp * x[0]) * a.dt)) + a.b * z[1];
+        y0 = lca_next_f64(x[0], x[1], d[0], a.leak, a.comp, a.dt, a.b, z[0]);
+        y1 = lca_next_f64(x[1], x[0], d[1], a.leak, a.comp, a.dt, a.b, z[1]);
       } else {
         const LcaF32 pf = lca_f32(a.leak, a.comp, a.dt, a.b);
         const float xf0 = (float)x[0], xf1 = (float)x[1];
