@@ -181,7 +181,9 @@ typedef struct {
  *                 stages block x ~64 bytes of LDS).  Other values, and other
  *                 kinds: CM_E_UNSUPPORTED.  The time-course variant runs 256.
  *  runs_per_lane  lane-per-run kernels: runs handed to a workgroup per lane
- *                 (0: chosen per launch from the run count, 2..8).
+ *                 (0: chosen per launch from the run count: 1..8, and
+ *                 fewer runs than lanes in a small launch, where a team of
+ *                 lanes holds each run).
  *  steps_per_sync lane-per-run kernels: steps between refills of finished
  *                 lanes (1..64; the DDM counts step pairs).  Defaults: 16
  *                 steps (LCA), 8 pairs (DDM).
@@ -191,7 +193,7 @@ typedef struct {
  *  lanes_per_run  DDM only: 1 (one lane per run), 64 (one wavefront per
  *                 run, 128 steps per prefix scan; runs_per_lane then counts
  *                 runs per wavefront) or 0 (per launch: 64 when every sweep
- *                 of the launch has at most 2^20 runs, else 1).  The
+ *                 of the launch has at most 2^18 runs, else 1).  The
  *                 wavefront form runs 8 wavefronts per workgroup when the
  *                 launch has at most 2^17 runs, else 4 (the block knob
  *                 does not apply to it).

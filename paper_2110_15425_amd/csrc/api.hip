@@ -415,11 +415,13 @@ cm_status check_launch(const cm_model* m, const cm_sweep* s, const cm_result* r,
 
 // The DDM's wavefront-per-run scan cuts a run's latency 64-fold at similar
 // work per step; it wins while the sweep is too small to fill the GPU with
-// lanes (measured on MI355X: 16x faster at 10^4 runs, 1.4x slower at 10^7).
+// lanes (measured on MI355X, us per sweep, scan against lanes: FP64 20 / 44 at
+// 10^4 runs, 149 / 149 at 2.5x10^5, 268 / 220 at 5x10^5; FP32 steps 18 / 38,
+// 122 / 121, 217 / 155).
 bool scan_ddm(const cm_tuning& t, uint64_t runs) {
   if (t.lanes_per_run == 64) return true;
   if (t.lanes_per_run == 1) return false;
-  return runs <= (1ull << 20);
+  return runs <= (1ull << 18);
 }
 
 // Time course requested with a launch: output [settings][K][6] and the
@@ -485,13 +487,11 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
   a.pf = cm::lca_f32(a.leak, a.comp, a.dt, a.b);
   a.bf = (float)a.b;
   a.guard_f = (float)(a.thresh - 2.0 * a.flag_eps);
-  // Few runs per lane keep every SIMD busy when the launch is small (the tail
-  // of long runs dominates); more runs per lane amortise the end of each
-  // workgroup's chunk when the launch is large, until too few workgroups are
-  // left to balance the GPU.  Measured on MI355X: 2 for ~10^5-10^6 runs, 6-8
-  // for ~10^7.
   uint64_t rpl = tune.runs_per_lane;
   uint64_t chunk;
+  // a draining workgroup packs its last runs into one wavefront; where the
+  // launch leaves issue slots idle anyway it spreads them over all its lanes
+  a.team_lanes = 64;
   if (scan) {
     // One wavefront per run: a workgroup of W wavefronts takes W runs per
     // round.  More runs per wavefront lengthen each wavefront's serial chain;
@@ -507,8 +507,33 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
           1, std::min<uint64_t>(64, (uint64_t)llround(4.0 * sqrt((double)runs / 600.0) / waves)));
     chunk = (uint64_t)waves * rpl;
   } else {
-    if (!rpl) rpl = std::max<uint64_t>(2, std::min<uint64_t>(8, launch_runs / (4096ull * h->cu_count)));
-    chunk = (uint64_t)block * rpl;
+    const uint64_t cus = (uint64_t)h->cu_count;
+    const uint64_t once = cus * cm::lane_groups_per_cu((int)m->kind, (int)m->precision) * 256ull;  // runs of
+    // one run per lane that the GPU holds at a time
+    if (rpl) {
+      chunk = (uint64_t)block * rpl;
+    } else if (launch_runs <= once) {
+      // Four workgroups per compute unit up to 2^16 runs, two up to 2^17, each
+      // run held by a team of lanes from the start; then one run per lane.
+      // Measured on MI355X, conflict network, us per sweep, against two runs
+      // per lane: 999 runs FP64 90 to 26, FP32 72 to 25; 32,000 runs 101 to 50
+      // and 80 to 46 (two workgroups per compute unit: 57, 52); 96,000 runs 101
+      // to 76 and 80 to 63 (four: 79, 69); 256,000 runs 124 to 114 and 92 to
+      // 85.  Drains spread over all lanes of the workgroup up to 2^18 runs: at
+      // 96,000 runs 84 to 77 and 67 to 63, at 409,600 FP32 120 to 127.
+      const uint64_t groups_want = cus * (launch_runs <= (1ull << 16) ? 4u : 2u);
+      chunk = std::max<uint64_t>(4, std::min<uint64_t>(block, (launch_runs + groups_want - 1) / groups_want));
+      if (launch_runs <= (1ull << 18)) a.team_lanes = block;
+    } else {
+      // As many runs per lane as let the GPU hold every workgroup at once, up
+      // to 4; larger launches take several rounds of workgroups.  640,000 runs,
+      // 1 / 2 / 3 runs per lane: FP64 218 / 199 / 221 us, FP32 141 / 133 / 144;
+      // drift-diffusion of 10^6 runs, FP64, 2 / 3 / 4: 345 / 338 / 331; 10^7
+      // runs FP64, 4 / 6 / 8: 2115 / 2077 / 2106.
+      rpl = (launch_runs + once - 1) / once;
+      if (rpl > 4) rpl = std::max<uint64_t>(3, std::min<uint64_t>(8, launch_runs / (4096ull * cus)));
+      chunk = (uint64_t)block * rpl;
+    }
   }
   chunk = std::min<uint64_t>(chunk, kMaxChunk);
   if (tc.every) {

@@ -27,6 +27,7 @@ constexpr size_t kNormTabBytes = 4096;
 struct SimArgs {
   uint64_t trials, n_settings, total_runs, seed;
   uint64_t chunk;     // runs handed to one workgroup
+  uint32_t team_lanes;  // lanes a draining workgroup spreads its last runs over (64 .. its size)
   uint32_t max_steps, n_bins, n_signals, window, steps_per_sync;
   double thresh, flag_eps, b, dt;
   double drift, start;  // DDM
@@ -258,6 +259,9 @@ hipError_t launch_queue(int kind, int precision, const QueueArgs& q, uint32_t gr
 // LDS after the histogram window (and the time-course blocks) that the lane
 // kernel uses to pack unfinished runs while a chunk drains.
 size_t lane_stage_bytes(int kind, int precision, uint32_t block);
+// Lane-kernel workgroups of 256 threads that a compute unit holds at a time
+// (compiler's register allocation).
+uint32_t lane_groups_per_cu(int kind, int precision);
 hipError_t launch_score(const ScoreBatch& b, hipStream_t st);
 uint32_t loop_team_lanes(uint32_t J, uint64_t runs, uint32_t cus);
 hipError_t launch_loop(int precision, const LoopArgs& a, uint32_t team, uint32_t blocks, hipStream_t st);

@@ -33,6 +33,10 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kScanBlockMax = 512;  // the scan kernel runs 256 or 512 threads per workgroup
 constexpr int kDrainSteps = 16;  // steps between packings once a chunk's queue is empty
+// Steps (pairs for the DDM) between packings while lane teams drain, and the
+// steps of a team's loop taken between two looks at the threshold.
+constexpr uint32_t kTeamSteps = 32;
+constexpr uint32_t kTeamGroup = 4;
 
 struct Lane {
   uint32_t s, t;   // setting, trial
@@ -42,6 +46,7 @@ struct Lane {
   bool flag;
   uint32_t next_sample;  // time-course variant: next sample step
   uint32_t sample_k;     // time-course variant: index of that sample
+  bool lead;             // time-course variant: the lane that adds its run's samples
 };
 
 // A lane's bookkeeping as it is staged through LDS while a workgroup drains
@@ -109,7 +114,7 @@ struct Sample {
     if (__builtin_expect(L.n == L.next_sample, 0)) {
       L.next_sample += every;
       const uint32_t k = L.sample_k++;
-      tc_add(base + ((uint64_t)(L.s - s_lo) * K + k) * kTcWords, x0, x1, comp);
+      if (L.lead) tc_add(base + ((uint64_t)(L.s - s_lo) * K + k) * kTcWords, x0, x1, comp);
     }
   }
 };
@@ -231,10 +236,33 @@ __device__ __forceinline__ uint64_t opaque_s(uint64_t v) {
   return v;
 }
 
+// One block's pair of normals (or increments) as a team passes it through LDS.
+template <int PREC>
+struct ZPair {
+  typename std::conditional<PREC == CM_FP64, double, float>::type a, b;
+};
+
+// Orders a wavefront's LDS stores before its other lanes' loads of them, and
+// those before the next stores (its LDS instructions execute in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // Mechanisms.  Each model provides: begin(lane) -- set up a run; advance() --
 // execute up to `steps` steps (a step pair per random block for the DDM),
-// returning false once the run has ended; state() for dumps.
+// returning false once the run has ended; advance_team() -- the same for a
+// run held by a team of lanes; state() for dumps.
+//
+// A team is 2..64 aligned lanes holding the same run.  Its lanes draw as many
+// consecutive blocks of the run at once, pass the normals round through LDS
+// and then all take the steps one after the other, with the same operations
+// in the same order as a single lane: a run then waits for the random
+// numbers once per team round instead of once per step, and only the update's
+// own chain (36 cycles in FP64, 54 in FP32 steps) is left.  A team looks at the
+// threshold once per kTeamGroup steps; when a run came near it in a group, the
+// group is taken again from its start, step by step.
 //
 // The step loops count with a wave-uniform counter k: a run's step number is
 // its steps before the call, n0, plus k, and enters the random numbers only
@@ -250,6 +278,12 @@ __device__ __forceinline__ uint64_t opaque_s(uint64_t v) {
 template <int PREC>
 struct DDM {
   static constexpr int kPrec = PREC;
+  static constexpr bool kClips = false;
+  // Wavefronts per SIMD the kernel is built for when the tuning names none:
+  // the double-precision polynomials' constants would take 94 registers (98 in
+  // the LCA) and leave 5 (4).  10^7 FP64 runs 2.10 ms at 6, 2.14 at 5; the LCA
+  // spills at 6: 64 x 10^4 FP64 runs 199 us at 5, 203 at 4, 220 at 6.
+  static constexpr int kWaves = PREC == CM_FP64 ? 6 : 7;
   double x, a_step;
   RunKey rk;
   static constexpr int kWidth = 1;
@@ -262,14 +296,31 @@ struct DDM {
     rk = run_key(L.t, L.s, k0, k1);
   }
 
-  // One step from normal z (zf in FP32 steps); false once the run has ended
-  // (L.n is then its decision step n).  guard = thresh - 2 eps: nearer the
-  // origin no bound is within flag distance.
+  using Z = ZPair<PREC>;  // the normals in FP64, the increments in FP32 steps
+
+  __device__ __forceinline__ Z draw(const SimArgs& A, const Words& w, const NormTab* nt) const {
+    Z z;
+    if constexpr (PREC == CM_FP64) {
+      normals64(w, *nt, z.a, z.b);
+    } else {
+      normals32(w, z.a, z.b);
+      z.a = fmaf(A.bf, z.a, (float)a_step);
+      z.b = fmaf(A.bf, z.b, (float)a_step);
+    }
+    return z;
+  }
+
+  __device__ __forceinline__ void move(const SimArgs& A, decltype(Z::a) z) {
+    if constexpr (PREC == CM_FP64) x = __builtin_fma(A.b, z, x + a_step);
+    else x = x + (double)z;
+  }
+
+  // One step; false once the run has ended (L.n is then its decision step n).
+  // guard = thresh - 2 eps: nearer the origin no bound is within flag distance.
   template <class H>
-  __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, double z, float zf,
-                                      float af, double guard, const H& hook) {
-    if (PREC == CM_FP64) x = __builtin_fma(A.b, z, x + a_step);
-    else x = x + (double)fmaf(A.bf, zf, af);
+  __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, decltype(Z::a) z, double guard,
+                                      const H& hook) {
+    move(A, z);
     if constexpr (H::kPerStep) {
       L.n = n;
       hook(L, x, 0.0);
@@ -291,22 +342,34 @@ struct DDM {
   template <class H>
   __device__ __forceinline__ bool pairs_loop(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1,
                                              uint32_t pairs, const NormTab* nt, const H& hook) {
-    const float af = (float)a_step;
     const double guard = A.thresh - 2.0 * A.flag_eps;
     const uint32_t n0 = L.n, b0 = n0 >> 1;  // a running lane enters at an even step count
     uint64_t kM = 0;
     for (uint32_t p = 0; p < pairs; ++p) {
-      const Words w = philox_run(b0, opaque_s(kM), rk, k0, k1);
-      double z0 = 0, z1 = 0;
-      float f0 = 0, f1 = 0;
-      if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
-      else normals32(w, f0, f1);
+      const Z z = draw(A, philox_run(b0, opaque_s(kM), rk, k0, k1), nt);
       const uint32_t n = n0 + 2u * p;
-      if (!one(A, L, n + 1u, z0, f0, af, guard, hook)) return false;
-      if (!one(A, L, n + 2u, z1, f1, af, guard, hook)) return false;
+      if (!one(A, L, n + 1u, z.a, guard, hook)) return false;
+      if (!one(A, L, n + 2u, z.b, guard, hook)) return false;
       kM += kPhiloxM0;
     }
     L.n = n0 + 2u * pairs;
+    return true;
+  }
+
+  // After whole pairs: an odd cap's own step, and the cap itself.
+  template <class H>
+  __device__ __forceinline__ bool at_cap(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1, const NormTab* nt,
+                                         const H& hook) {
+    if (L.n + 1u == A.max_steps) {  // first of a pair
+      const Z z = draw(A, philox_run(L.n >> 1, 0ull, rk, k0, k1), nt);
+      const uint32_t n = L.n + 1u;
+      if (!one(A, L, n, z.a, A.thresh - 2.0 * A.flag_eps, hook)) return false;
+      L.n = n;
+    }
+    if (L.n == A.max_steps) {  // reached without a crossing
+      L.choice = -1;
+      return false;
+    }
     return true;
   }
 
@@ -318,21 +381,47 @@ struct DDM {
                                           int pairs, const NormTab* nt, const H& hook) {
     const uint32_t t = uniform_trips((uint32_t)pairs, (A.max_steps - L.n) >> 1);
     if (!pairs_loop(A, L, k0, k1, t, nt, hook)) return false;
-    if (L.n + 1u == A.max_steps) {  // an odd cap's own step, first of a pair
-      const Words w = philox_run(L.n >> 1, 0ull, rk, k0, k1);
-      double z0 = 0, z1 = 0;
-      float f0 = 0, f1 = 0;
-      if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
-      else normals32(w, f0, f1);
-      const uint32_t n = L.n + 1u;
-      if (!one(A, L, n, z0, f0, (float)a_step, A.thresh - 2.0 * A.flag_eps, hook)) return false;
-      L.n = n;
+    return at_cap(A, L, k0, k1, nt, hook);
+  }
+
+  // Up to `team` pairs of a run held by `team` lanes (sub: this lane's place
+  // in it; zs: the team's entries of the wavefront's LDS buffer).
+  template <bool, class H>
+  __device__ __forceinline__ bool advance_team(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1, uint32_t team,
+                                               uint32_t sub, Z* zs, const NormTab* nt, const H& hook) {
+    const double guard = A.thresh - 2.0 * A.flag_eps;
+    const uint32_t n0 = L.n, t = uniform_trips(team, (A.max_steps - n0) >> 1);
+    zs[sub] = draw(A, philox_run((n0 >> 1) + sub, 0ull, rk, k0, k1), nt);
+    wave_sync();
+    uint32_t p = 0, end = t;
+    if constexpr (!H::kPerStep) {
+      for (; p + kTeamGroup <= t; p += kTeamGroup) {
+        const double before = x;
+        bool near = false;
+#pragma unroll
+        for (uint32_t g = 0; g < kTeamGroup; ++g) {
+          const Z z = zs[p + g];
+          move(A, z.a);
+          near |= fabs(x) >= guard;
+          move(A, z.b);
+          near |= fabs(x) >= guard;
+        }
+        if (near) {  // this group again, step by step
+          x = before;
+          end = p + kTeamGroup;
+          break;
+        }
+      }
     }
-    if (L.n == A.max_steps) {  // the cap, reached without a crossing
-      L.choice = -1;
-      return false;
+    for (; p < end; ++p) {
+      const Z z = zs[p];
+      const uint32_t n = n0 + 2u * p;
+      if (!one(A, L, n + 1u, z.a, guard, hook)) return false;
+      if (!one(A, L, n + 2u, z.b, guard, hook)) return false;
     }
-    return true;
+    L.n = n0 + 2u * p;
+    wave_sync();
+    return at_cap(A, L, k0, k1, nt, hook);
   }
 
   __device__ __forceinline__ void state(double* out) const { out[0] = x; }
@@ -383,6 +472,8 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   double x0, x1;
   RunKey rk;
   static constexpr int kPrec = PREC;
+  static constexpr bool kClips = true;  // SimArgs::nonneg applies
+  static constexpr int kWaves = PREC == CM_FP64 ? 5 : 7;  // see DDM
   static constexpr int kWidth = 2;
 
   __device__ __forceinline__ void begin(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1) {
@@ -401,50 +492,63 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
     rk = run_key(L.t, L.s, k0, k1);
   }
 
-  // One step from the block w; false when the new state is near the
-  // threshold (L.n is then n).  xf0, xf1: the float images of the state
+  using Z = ZPair<PREC>;
+
+  __device__ __forceinline__ Z draw(const Words& w, const NormTab* nt) const {
+    Z z;
+    if constexpr (PREC == CM_FP64) normals64(w, *nt, z.a, z.b);
+    else normals32(w, z.a, z.b);
+    return z;
+  }
+
+  // The update from the normals z.  xf0, xf1: the float images of the state
   // (FP32 steps).
-  template <class H>
-  __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, const Words& w,
-                                      float& xf0, float& xf1, const NormTab* nt, const H& hook) {
+  __device__ __forceinline__ void move(const SimArgs& A, const Z& z, bool nonneg, float& xf0, float& xf1) {
     double y0, y1;
     if constexpr (PREC == CM_FP64) {
-      double z0, z1;
-      normals64(w, *nt, z0, z1);
-      y0 = lca_next_f64(x0, x1, this->in0, A.leak, A.comp, A.dt, A.b, z0);
-      y1 = lca_next_f64(x1, x0, this->in1, A.leak, A.comp, A.dt, A.b, z1);
+      y0 = lca_next_f64(x0, x1, this->in0, A.leak, A.comp, A.dt, A.b, z.a);
+      y1 = lca_next_f64(x1, x0, this->in1, A.leak, A.comp, A.dt, A.b, z.b);
     } else {
-      float z0, z1;
-      normals32(w, z0, z1);
-      y0 = x0 + (double)lca_inc_f32(A.pf, this->idt0, xf0, xf1, z0);
-      y1 = x1 + (double)lca_inc_f32(A.pf, this->idt1, xf1, xf0, z1);
+      y0 = x0 + (double)lca_inc_f32(A.pf, this->idt0, xf0, xf1, z.a);
+      y1 = x1 + (double)lca_inc_f32(A.pf, this->idt1, xf1, xf0, z.b);
     }
-    if (A.nonneg) {
+    if (nonneg) {
       if (y0 < 0.0) y0 = 0.0;
       if (y1 < 0.0) y1 = 0.0;
     }
     x0 = y0;
     x1 = y1;
+    if constexpr (PREC != CM_FP64) {
+      xf0 = (float)x0;
+      xf1 = (float)x1;
+    }
+  }
+
+  // One cheap comparison per step: a lane whose new state is within 2 eps
+  // of the threshold (or across it) leaves the loop at this step, and the
+  // exact tests run once after the loop (advance).  FP32 steps compare the
+  // float images of the new state (which the next step needs anyway) with
+  // the float image of the guard: rounding is monotone, so x >= guard
+  // implies float(x) >= float(guard).
+  __device__ __forceinline__ bool near(const SimArgs& A, float xf0, float xf1) const {
+    if constexpr (PREC == CM_FP64) {
+      const double guard = A.thresh - 2.0 * A.flag_eps;
+      return (x0 >= guard) | (x1 >= guard);
+    } else {
+      return (xf0 >= A.guard_f) | (xf1 >= A.guard_f);
+    }
+  }
+
+  // One step; false when the new state is near the threshold (L.n is then n).
+  template <class H>
+  __device__ __forceinline__ bool one(const SimArgs& A, Lane& L, uint32_t n, const Z& z, bool nonneg, float& xf0,
+                                      float& xf1, const H& hook) {
+    move(A, z, nonneg, xf0, xf1);
     if constexpr (H::kPerStep) {
       L.n = n;
       hook(L, x0, x1);
     }
-    // one cheap comparison per step: a lane whose new state is within 2 eps
-    // of the threshold (or across it) leaves the loop at this step, and the
-    // exact tests run once after the loop (advance).  FP32 steps compare the
-    // float images of the new state (which the next step needs anyway) with
-    // the float image of the guard: rounding is monotone, so x >= guard
-    // implies float(x) >= float(guard).
-    bool near;
-    if constexpr (PREC == CM_FP64) {
-      const double guard = A.thresh - 2.0 * A.flag_eps;
-      near = (x0 >= guard) | (x1 >= guard);
-    } else {
-      xf0 = (float)x0;
-      xf1 = (float)x1;
-      near = (xf0 >= A.guard_f) | (xf1 >= A.guard_f);
-    }
-    if (near) {
+    if (near(A, xf0, xf1)) {
       L.n = n;
       return false;
     }
@@ -460,11 +564,25 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
     float xf0 = (float)x0, xf1 = (float)x1;
     uint64_t kM = 0;
     for (uint32_t k = 0; k < steps; ++k) {
-      const Words w = philox_run(n0, opaque_s(kM), rk, k0, k1);
-      if (!one(A, L, n0 + k + 1u, w, xf0, xf1, nt, hook)) return false;
+      const Z z = draw(philox_run(n0, opaque_s(kM), rk, k0, k1), nt);
+      if (!one(A, L, n0 + k + 1u, z, A.nonneg != 0u, xf0, xf1, hook)) return false;
       kM += kPhiloxM0;
     }
     L.n = n0 + steps;
+    return true;
+  }
+
+  // Stopped near the threshold after step L.n: the exact tests; true when the
+  // run goes on (within 2 eps below the threshold).
+  __device__ __forceinline__ bool settle(const SimArgs& A, Lane& L) const {
+    const double th = A.thresh, eps = A.flag_eps;
+    if (near_th(x0, th, eps) || near_th(x1, th, eps)) L.flag = true;
+    const double mx = x0 > x1 ? x0 : x1;
+    if (mx >= th) {
+      L.choice = (x1 > x0) ? 1 : 0;
+      if (fabs(x0 - x1) < eps) L.flag = true;
+      return false;
+    }
     return true;
   }
 
@@ -473,18 +591,55 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
                                           int steps, const NormTab* nt, const H& hook) {
     // the step cap bounds the trip count, so the body needs no cap test
     const uint32_t t = uniform_trips((uint32_t)steps, A.max_steps - L.n);
-    if (!steps_loop(A, L, k0, k1, t, nt, hook)) {
-      // stopped near the threshold after step L.n: the exact tests
-      const double th = A.thresh, eps = A.flag_eps;
-      if (near_th(x0, th, eps) || near_th(x1, th, eps)) L.flag = true;
-      const double mx = x0 > x1 ? x0 : x1;
-      if (mx >= th) {
-        L.choice = (x1 > x0) ? 1 : 0;
-        if (fabs(x0 - x1) < eps) L.flag = true;
-        return false;
-      }
-      // within 2 eps below the threshold: the run goes on from step L.n
+    if (!steps_loop(A, L, k0, k1, t, nt, hook) && !settle(A, L)) return false;
+    if (L.n == A.max_steps) {  // the cap, reached without a crossing
+      L.choice = -1;
+      return false;
     }
+    return true;
+  }
+
+  // Up to `team` steps of a run held by `team` lanes (sub: this lane's place
+  // in it; zs: the team's entries of the wavefront's LDS buffer).  NN is
+  // A.nonneg at compile time: a uniform branch on it inside the first loop,
+  // which lanes leave at different iterations, is compiled to a lane mask of
+  // that loop's last iteration and then wrongly used for the second loop.
+  template <bool NN, class H>
+  __device__ __forceinline__ bool advance_team(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1, uint32_t team,
+                                               uint32_t sub, Z* zs, const NormTab* nt, const H& hook) {
+    const uint32_t n0 = L.n, t = uniform_trips(team, A.max_steps - n0);
+    zs[sub] = draw(philox_run(n0 + sub, 0ull, rk, k0, k1), nt);
+    wave_sync();
+    float xf0 = (float)x0, xf1 = (float)x1;
+    uint32_t k = 0, end = t;
+    if constexpr (!H::kPerStep) {
+      for (; k + kTeamGroup <= t; k += kTeamGroup) {
+        const double before0 = x0, before1 = x1;
+        bool stop = false;
+#pragma unroll
+        for (uint32_t g = 0; g < kTeamGroup; ++g) {
+          move(A, zs[k + g], NN, xf0, xf1);
+          stop |= near(A, xf0, xf1);
+        }
+        if (stop) {  // this group again, step by step
+          x0 = before0;
+          x1 = before1;
+          end = k + kTeamGroup;
+          break;
+        }
+      }
+      xf0 = (float)x0;
+      xf1 = (float)x1;
+    }
+    bool stopped = false;
+    for (; k < end; ++k)
+      if (!one(A, L, n0 + k + 1u, zs[k], NN, xf0, xf1, hook)) {
+        stopped = true;
+        break;
+      }
+    if (!stopped) L.n = n0 + k;
+    wave_sync();
+    if (stopped && !settle(A, L)) return false;
     if (L.n == A.max_steps) {  // the cap, reached without a crossing
       L.choice = -1;
       return false;
@@ -594,6 +749,7 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
     L.flag = false;
     L.next_sample = a.tc_every;
     L.sample_k = 0;
+    L.lead = true;
     m.begin(a, L, k0, k1);
   };
   if (have) setup(off);
@@ -616,13 +772,22 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
       if (have) setup(off);
     }
   }
-  // Drain: every kDrainSteps steps the workgroup packs its unfinished runs
-  // into the first wavefronts (through LDS); the wavefronts beyond the
-  // packed list wait at the barriers without issuing vector work, which
-  // leaves their issue slots to the other workgroups on the compute unit
-  // instead of stepping a few live lanes each.
+  // Drain: every so many steps the workgroup packs its unfinished runs into the
+  // first lanes (through LDS).  While more are left than half of a.team_lanes,
+  // one lane takes each: the wavefronts beyond the packed list wait at the
+  // barriers without issuing vector work, which leaves their issue slots to the
+  // other workgroups on the compute unit.  Fewer are spread over team_lanes
+  // lanes, a team of 2..64 lanes each: a few long runs would otherwise step at
+  // one lane's latency per random number.  In one wavefront (team_lanes 64) a
+  // team round also issues less than lanes of their own would: per step and
+  // FP32 run 52 / K + 14 instructions in K lanes against 62 in a wavefront of
+  // mostly idle lanes.
+  using Z = typename M::Z;
   M* stage_m = (M*)(lds + a.window * (rec_words(a.n_bins) + (TC ? tc_words(a.tc_k) : 0u)));
   LaneWords* stage_l = (LaneWords*)(stage_m + BLOCK);
+  // teams stage at most BLOCK / 2 runs: their normals go behind those
+  Z* zbuf = (Z*)(stage_m + BLOCK / 2);
+  static_assert(BLOCK * sizeof(Z) <= BLOCK / 2 * sizeof(M), "the normals fit behind half of the stage");
   const uint32_t w = threadIdx.x >> 6, lane = threadIdx.x & 63u;
   const uint64_t below = (1ull << lane) - 1ull;
   for (;;) {
@@ -635,6 +800,7 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
       if (v < w) base += drain_cnt[v];
       total += drain_cnt[v];
     }
+    total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);  // the same in every lane
     if (have) {
       const uint32_t i = base + (uint32_t)__popcll(act & below);
       stage_m[i] = m;
@@ -642,7 +808,9 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
     }
     __syncthreads();
     if (total == 0) break;  // every run of the chunk is recorded
-    const uint32_t i = w * 64u + lane;
+    uint32_t shift = 0;  // team of 2^shift lanes
+    while (shift < 6u && (total << (shift + 1u)) <= a.team_lanes) ++shift;
+    const uint32_t i = threadIdx.x >> shift, sub = threadIdx.x & ((1u << shift) - 1u);
     have = i < total;
     if (have) {
       m = stage_m[i];
@@ -656,10 +824,25 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
       if constexpr (TC) {  // samples fall on multiples of tc_every
         L.sample_k = L.n / a.tc_every;
         L.next_sample = (L.sample_k + 1u) * a.tc_every;
+        L.lead = sub == 0;
       }
     }
     bool running = have;
-    if (__any(running)) running = running && m.advance(a, L, k0, k1, kDrainSteps, nt, hook);
+    if (shift == 0) {
+      if (__any(running)) running = running && m.advance(a, L, k0, k1, kDrainSteps, nt, hook);
+    } else {
+      Z* zs = zbuf + (threadIdx.x - sub);
+      auto rounds = [&](auto nonneg) {
+        for (uint32_t r = 0; r < kTeamSteps; r += 1u << shift) {
+          if (!__any(running)) break;
+          if (running)
+            running = m.template advance_team<decltype(nonneg)::value>(a, L, k0, k1, 1u << shift, sub, zs, nt, hook);
+        }
+      };
+      if (M::kClips && a.nonneg) rounds(std::true_type{});
+      else rounds(std::false_type{});
+      have = have && sub == 0;  // the team's first lane records or stages the run
+    }
     if (have && !running) {
       finish();
       have = false;
@@ -669,7 +852,7 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
 }
 
 template <class M, bool TC, int OCC, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(OCC ? OCC : 1)))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(OCC ? OCC : M::kWaves)))
 void sim_lane_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];  // 8-byte aligned window
   __shared__ uint32_t next;
@@ -1078,6 +1261,11 @@ hipError_t launch_queue(int kind, int precision, const QueueArgs& q, uint32_t gr
   else
     hipLaunchKernelGGL(queue_kernel<LCA<CM_FP32_STEP>>, dim3(groups), dim3(kBlock), lds_bytes, st, q);
   return hipGetLastError();
+}
+
+uint32_t lane_groups_per_cu(int kind, int precision) {  // 4 wavefronts each, 4 SIMDs
+  if (kind == CM_DDM) return precision == CM_FP64 ? DDM<CM_FP64>::kWaves : DDM<CM_FP32_STEP>::kWaves;
+  return precision == CM_FP64 ? LCA<CM_FP64>::kWaves : LCA<CM_FP32_STEP>::kWaves;
 }
 
 size_t lane_stage_bytes(int kind, int precision, uint32_t block) {
