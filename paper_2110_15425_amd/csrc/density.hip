@@ -11,8 +11,9 @@
 // tail.  The first step leaves the exact start point; later steps leave cell
 // centres (midpoint rule, error O(h^2)).
 //
-// One workgroup per setting keeps the kernel row and the mass vectors in LDS
-// for all steps.  The product T m is a dense contraction on the FP64 matrix
+// Where the step's width allows it the mass is propagated by its samples on a
+// coarser grid, 16 steps at a time (the coarse form below); else one workgroup
+// per setting keeps the kernel row and the mass vectors in LDS for all steps.  The product T m is a dense contraction on the FP64 matrix
 // cores: with cells grouped in blocks of 16, block-diagonal d of T is one
 // 16x16 matrix F_d (F_d[alpha][gamma] = f(16 d + alpha - gamma)), so
 //   y_block(a) = sum_d F_d m_block(a - d),
@@ -108,6 +109,543 @@ __host__ __device__ inline DensityGeo density_geo(uint32_t M) {
 
 namespace {
 
+// ---------------------------------------------------------------------------
+// Coarse propagation.
+//
+// After one step the survivor mass is a superposition of Gaussians of the
+// step's width b, so its spectrum above 8.9 / b is below 2^-57 of the whole:
+// as a function of the position it is determined by its samples s cells
+// apart, with s h <= pi b / 8.9 (h the cell width).  With those r samples v as
+// the state -- over the grid and 8.3 b beyond it, where the function has died
+// away -- a step is one r x r matrix,
+//   v' = B v,  B[p][q] = sum over cells i of f(X_p - i) sinc((i - X_q) / s),
+// f the kernel row, X_p = s (p - mg) the sample positions in cells: the mass of
+// cell i is interpolated from the samples and moved to sample p, the same sum
+// over cells as the full product (r is about 110 for 1000 cells where b is a
+// 20th of the range).  Up to 128 cells the samples are the cells themselves.
+// The sum over all integers i would be s f(X_p - X_q) by the sampling theorem,
+// so B is that minus the sums over the cells that are not there, i < 0 and
+// i >= M, and only rows within 8.7 b of a bound take any product.
+//
+// B, its squares and the powers up to B^16 are products on the FP64 matrix
+// cores from LDS; the outputs of 16 steps are W v with W's 48 rows w B^k (w
+// the absorption at either bound and the total, k = 0..15), built beside the
+// squarings by doubling.  One pass over (B^16, W), held in registers, then
+// advances 16 steps: 3000 steps are 188 passes.  The first steps, while the
+// mass at a bound is so small that the samples' absolute rounding would show
+// in it, are taken on the full grid.
+//
+// Precision: f comes from a Hermite expansion of the Gaussian's cell integral
+// (no cancellation), and the rounding of f and of B's Toeplitz part is corrected
+// so that they conserve mass, or a systematic relative error of 10^-16 per step
+// would grow with the steps.  Against an 80-bit propagation (14 cases of 120 to
+// 1300 cells; norm of the error over the norm of the result) 7.8e-16 on average
+// and 3.2e-15 at most, the full-grid form 8.1e-16 and 3.5e-15.
+//
+// Bound by the FP64 matrix cores of one compute unit per setting and, in the
+// passes, by latency.  64 drifts x 3000 steps x 1000 cells: 0.48 ms against
+// 20.4 on the full grid, of which the squarings 0.19, the passes 0.13 (0.7 us
+// each), B 0.08, the seven full-grid steps 0.05.
+// ---------------------------------------------------------------------------
+constexpr int kCoarse = 128;        // most samples (rows of B)
+constexpr int kCoarseThreads = 512;
+constexpr int kCoarsePow = 16;      // steps per pass
+
+struct CoarsePlan {
+  bool ok;
+  int s, mg, r;  // sample spacing (cells), samples beyond either end, samples
+  int E;         // displacement (cells) beyond which f is nothing
+  int direct;    // steps taken on the full grid
+};
+
+// LDS layout (doubles): the preparation's arrays, later overlaid by the powers.
+struct CoarseGeo {
+  int FO, SM;  // f table: displacements -FO .. FO; sinc table: 0 .. SM
+  int o_st, o_m0, o_m1, o_part, prep;
+};
+__host__ __device__ inline CoarseGeo coarse_geo(const DensityGeo& g, const CoarsePlan& p) {
+  CoarseGeo c;
+  const int need = p.E + 16 * p.s + 16;
+  c.FO = (int)g.FOFF > need ? (int)g.FOFF : need;
+  c.SM = (int)g.M + 2 * p.E + 2 * p.s + 16;
+  c.o_st = 2 * c.FO + 1;
+  c.o_m0 = c.o_st + c.SM + 1;
+  c.o_m1 = c.o_m0 + (int)g.CB * kBS;
+  c.o_part = c.o_m1 + (int)g.CB * kBS;
+  c.prep = c.o_part + 8 * 256;
+  return c;
+}
+constexpr int kWRows = 3 * kCoarsePow;                      // output rows
+constexpr int kVSeg = 34;                                    // LDS slots per 32 samples (two pads)
+constexpr int kOffW = kCoarse * kCoarse;                     // W's first 24 rows, behind B
+constexpr int kOffV = kOffW + (kWRows / 2) * kCoarse;        // [2][4 * kVSeg] samples
+constexpr int kCoarseLds = kOffV + 2 * 4 * kVSeg;            // doubles
+constexpr int kRing = 256;                                   // passes whose outputs LDS holds
+static_assert(kRing * kWRows <= kOffW, "the outputs fit over B");
+
+// Whether a setting propagates its samples instead of its cells: the samples
+// must be few enough and the kernel wide enough in cells, and neither bound so
+// unlikely (drift over noise) that its probabilities fall to the samples'
+// absolute rounding.  A NaN fails every test.
+__host__ __device__ inline CoarsePlan coarse_plan(uint32_t cells, double th, double b, double as, double start) {
+  CoarsePlan p{};
+  const double h = (2.0 * th) / (double)cells, bc = b / h, ac = fabs(as) / h;
+  if (!(bc >= 4.0) || !(2.0 * th >= 8.0 * b) || !(2.0 * fabs(as) * th <= 4.0 * b * b) || !(bc < 400.0)) return p;
+  if (cells <= (uint32_t)kCoarse) {
+    p.s = 1;
+    p.mg = 0;
+  } else {
+    p.s = (int)(3.14159265358979 * bc / 8.9);
+    if (p.s > 7) p.s -= 1 - (p.s & 1);  // odd: the strided reads of the tables spread over the LDS banks
+    if (p.s < 1) return p;
+    p.mg = (int)ceil((8.3 * bc + ac) / p.s);
+  }
+  p.r = ((int)cells - 1 + p.s - 1) / p.s + 1 + 2 * p.mg;
+  p.E = (int)ceil(8.7 * bc + ac) + 1;
+  const double far = (th + fabs(start)) / (3.8 * b), d = ceil(far * far);
+  p.direct = d < 1.0 ? 1 : d > 31.0 ? 31 : (int)d;
+  p.ok = p.r <= kCoarse && d <= 31.0 && coarse_geo(density_geo(cells), p).prep <= kCoarseLds;
+  return p;
+}
+
+// Slot of element (i, j) of a 128-column matrix: rows rotated against each
+// other by an exclusive or, so that a column of 16 rows spreads over the banks.
+__device__ __forceinline__ int mat_at(int i, int j) { return i * kCoarse + (j ^ ((i & 15) << 1)); }
+__device__ __forceinline__ int seg_at(int q) { return (q >> 5) * kVSeg + (q & 31); }
+
+// Gaussian mass of the unit cell at displacement d cells: the integral of the
+// normal density over [z - e/2, z + e/2], z = (d h - as) / b, e = h / b, as its
+// expansion in e (even Hermite polynomials; e <= 1/4, next term below 2^-55 of
+// the centre's value).
+__device__ double cell_mass(double d, double h, double as, double b) {
+  const double z = (d * h - as) / b, e = h / b, x = z * z, t = 0.25 * e * e;
+  const double h2 = x - 1.0, h4 = (x - 6.0) * x + 3.0, h6 = ((x - 15.0) * x + 45.0) * x - 15.0;
+  const double h8 = (((x - 28.0) * x + 210.0) * x - 420.0) * x + 105.0;
+  const double h10 = ((((x - 45.0) * x + 630.0) * x - 3150.0) * x + 4725.0) * x - 945.0;
+  double v = h10 * (t * (1.0 / 39916800.0));
+  v = t * (h8 * (1.0 / 362880.0) + v);
+  v = t * (h6 * (1.0 / 5040.0) + v);
+  v = t * (h4 * (1.0 / 120.0) + v);
+  v = t * (h2 * (1.0 / 6.0) + v);
+  return exp(-0.5 * x) * (0.39894228040143267794 * e) * (1.0 + v);
+}
+
+__global__ __launch_bounds__(kCoarseThreads) void ddm_density_coarse_kernel(DensityArgs a) {
+  extern __shared__ double sh[];
+  __shared__ double red[3][kCoarseThreads / 64];
+  __shared__ double resid_s;
+  __shared__ double first[2][32];  // outputs of the full-grid steps
+  const DensityGeo geo = density_geo(a.cells);
+  const int tid = (int)threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
+  const int wave = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
+  const uint64_t st = blockIdx.x;
+  const double drift = a.n_signals ? a.grid[st * a.n_signals] : a.drift;
+  const double as = drift * a.dt, b = a.b, th = a.thresh, h = (2.0 * th) / (double)a.cells;
+  CoarsePlan pl = coarse_plan(a.cells, th, b, as, a.start);
+  if (!pl.ok) return;  // the full-grid kernel's setting
+  for (int* v : {&pl.s, &pl.mg, &pl.r, &pl.E, &pl.direct}) *v = __builtin_amdgcn_readfirstlane(*v);  // scalars
+  const CoarseGeo cg = coarse_geo(geo, pl);
+  const int M = (int)a.cells, NB = (int)geo.NB, NT = (int)geo.NT, s = pl.s, r = pl.r, N = (int)a.max_steps;
+  double* out_lo = a.out + (st * 2u) * a.max_steps;
+  double* out_up = out_lo + a.max_steps;
+  double* ft = sh;
+  double* sc = sh + cg.o_st;
+  double* cur = sh + cg.o_m0;
+  double* nxt = sh + cg.o_m1;
+  double* part = sh + cg.o_part;
+
+  for (int x = tid; x < 2 * (int)geo.CB * kBS; x += kCoarseThreads) cur[x] = 0.0;
+  for (int x = tid; x <= 2 * cg.FO; x += kCoarseThreads) {
+    const int d = x - cg.FO;
+    ft[x] = d >= -pl.E && d <= pl.E ? cell_mass((double)d, h, as, b) : 0.0;
+  }
+  for (int x = tid; x <= cg.SM; x += kCoarseThreads)
+    sc[x] = x == 0 ? 1.0 : sinpi((double)(x % (2 * s)) / (double)s) * (double)s / (3.14159265358979323846 * (double)x);
+  __syncthreads();
+
+  // The mass that rounding leaves out of the kernel's row, 1 - sum of step f(step k),
+  // summed exactly by the first wavefront.
+  auto missing = [&](int step) {
+    double hi = 0.0, lo = 0.0;
+    const int kmax = pl.E / step;
+    for (int k = -kmax + lane; k <= kmax; k += 64) {
+      const double v = (double)step * ft[cg.FO + step * k], t = hi + v, bb = t - hi;
+      lo += (hi - (t - bb)) + (v - bb);
+      hi = t;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ohi = __shfl_xor(hi, o, 64), olo = __shfl_xor(lo, o, 64);
+      const double t = hi + ohi, bb = t - hi;
+      lo = (lo + olo) + ((hi - (t - bb)) + (ohi - bb));
+      hi = t;
+    }
+    if (lane == 0) resid_s = (1.0 - hi) - lo;
+  };
+  if (wave == 0) {
+    missing(1);
+    // to the entries one b either side, where it acts as it does spread over all
+    // of them in proportion
+    if (lane == 0) {
+      const int d1 = (int)(b / h + 0.5);
+      ft[cg.FO + d1] += 0.5 * resid_s;
+      ft[cg.FO - d1] += 0.5 * resid_s;
+    }
+  }
+  __syncthreads();
+
+  // This thread's cells of the full-grid steps, as in the full-grid kernel.
+  constexpr int kSlots = 3;
+  double upc[kSlots], loc[kSlots];
+  int pos[kSlots], cell[kSlots];
+  double sv = 0.0, pu = 0.0, pw = 0.0;
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k) {
+    const int t = tid + k * kCoarseThreads;
+    const int tt = t >> 8, rr = (t >> 6) & 3, l = t & 63;
+    const int blk = 16 * tt + (l & 15), j = 16 * blk + 4 * rr + (l >> 4);
+    cell[k] = t < 256 * NT && j < M ? j : -1;
+    pos[k] = t < 256 * NT ? (blk + NB) * kBS + 4 * rr + (l >> 4) : -1;
+    upc[k] = loc[k] = 0.0;
+    if (cell[k] >= 0) {
+      const double c = -th + ((double)j + 0.5) * h;
+      upc[k] = Phi(-((th - c) - as) / b);
+      loc[k] = Phi(((-th - c) - as) / b);
+      const double e0 = -th + (double)j * h, e1 = -th + (double)(j + 1) * h;
+      const double v = Phi(((e1 - a.start) - as) / b) - Phi(((e0 - a.start) - as) / b);
+      cur[pos[k]] = v;
+      pu = fma(v, upc[k], pu);
+      pw = fma(v, loc[k], pw);
+    }
+  }
+  // Full-grid steps: the mass after step n in cur, absorbed next in (pu, pw).
+  const int dlo = -((pl.E + 15) / 16) - 1, dhi = (pl.E + 15) / 16 + 1;
+  const int G = 8 / NT > 1 ? 8 / NT : 1, tile = wave / G, grp = wave - tile * G, c0 = 16 * tile;
+  const int dA = max(dlo, c0 - NB + 1), dB = min(dhi, min(c0 + 15, NB - 1));
+  const int nd = dB >= dA ? dB - dA + 1 : 0;
+  const int dS = dA + (nd * grp) / G, dE = dA + (nd * (grp + 1)) / G;
+  if (tid == 0) {
+    out_up[0] = Phi(-((th - a.start) - as) / b);
+    out_lo[0] = Phi(((-th - a.start) - as) / b);
+  }
+  int n = 1;
+  for (;; ++n) {
+    // sums of the mass after step n
+    pu = wave_sum(pu);
+    pw = wave_sum(pw);
+    sv = wave_sum(sv);
+    if (lane == 0) {
+      red[0][wave] = sv;
+      red[1][wave] = pu;
+      red[2][wave] = pw;
+    }
+    __syncthreads();  // sums, and the new mass in cur
+    double tv = 0.0, tu = 0.0, tl = 0.0;
+    for (int w = 0; w < kCoarseThreads / 64; ++w) {
+      tv += red[0][w];
+      tu += red[1][w];
+      tl += red[2][w];
+    }
+    if (n >= 2 && tv < a.tol) {  // as the full-grid kernel stops
+      for (int k = 1 + tid; k < N; k += kCoarseThreads) {
+        out_up[k] = k < n ? first[0][k] : 0.0;
+        out_lo[k] = k < n ? first[1][k] : 0.0;
+      }
+      return;
+    }
+    if (tid == 0) {
+      first[0][n] = tu;
+      first[1][n] = tl;
+    }
+    if (n == pl.direct) break;
+    f64x4 C = {0.0, 0.0, 0.0, 0.0};
+    if (tile < NT) {
+      const double* fa = ft + cg.FO + l16 - l4;
+      const double* mb = cur + (c0 + l16 + NB) * kBS + l4;
+      for (int d = dS; d < dE; ++d) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          C = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[16 * d - 4 * q], mb[4 * q - d * kBS], C, 0, 0, 0);
+      }
+      double* pp = part + ((grp * NT + tile) * 4) * 64 + lane;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) pp[k * 64] = C[k];
+    }
+    __syncthreads();
+    sv = 0.0;
+    pu = 0.0;
+    pw = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSlots; ++k) {
+      if (pos[k] >= 0) {
+        const int t = tid + k * kCoarseThreads;
+        double v = part[t];
+        for (int g = 1; g < G; ++g) v += part[t + g * NT * 256];
+        if (cell[k] < 0) v = 0.0;
+        nxt[pos[k]] = v;
+        sv += v;
+        pu = fma(v, upc[k], pu);
+        pw = fma(v, loc[k], pw);
+      }
+    }
+    double* t = cur;
+    cur = nxt;
+    nxt = t;
+  }
+  __syncthreads();  // every thread has read the sums; nxt is free
+  if (tid >= 1 && tid <= n) {  // (the launch rule leaves more steps than these)
+    out_up[tid] = first[0][tid];
+    out_lo[tid] = first[1][tid];
+  }
+  double* ua = nxt;  // absorption at either bound by cell, [2][M]
+#pragma unroll
+  for (int k = 0; k < kSlots; ++k)
+    if (cell[k] >= 0) {
+      ua[cell[k]] = upc[k];
+      ua[M + cell[k]] = loc[k];
+    }
+  if (wave == 0) missing(s);  // of B's Toeplitz part
+  __syncthreads();
+  // It goes to the entries one b either side again; what their rounding leaves
+  // goes to those three b away, whose own rounding is small.
+  const int k1 = (int)(b / (h * s) + 0.5), k3 = (int)(3.0 * b / (h * s));
+  const double gu = (double)s * ft[cg.FO + s * k1], gd = (double)s * ft[cg.FO - s * k1];
+  const double gur = gu + 0.5 * resid_s, gdr = gd + 0.5 * resid_s;
+  const double rest = 0.5 * (resid_s - ((gur - gu) + (gdr - gd)));
+
+  // The samples after the next step, and w in the samples: sums over cells in
+  // four parts, one sample or column per thread, by blocks of 16 cells (their
+  // rounding is in every output alike).
+  const int q = tid & (kCoarse - 1), qc = q < r ? q : r - 1, quarter = tid >> 7;
+  const int Xq = s * (qc - pl.mg);
+  double v0 = 0.0, w0 = 0.0, w1 = 0.0, w2 = 0.0;
+  for (int blk = quarter; blk < NB; blk += 4) {
+    const double* mb = cur + (blk + NB) * kBS;
+    const int i1 = min(16, M - 16 * blk);
+    double bv = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0;
+    for (int k = 0; k < i1; ++k) {
+      const int i = 16 * blk + k, d = Xq - i;
+      const int dc = d < -cg.FO ? -cg.FO : d > cg.FO ? cg.FO : d;  // f is 0 at either end of its table
+      bv = fma(ft[cg.FO + dc], mb[k], bv);
+      const double S = sc[d < 0 ? -d : d];
+      b0 = fma(ua[i], S, b0);
+      b1 = fma(ua[M + i], S, b1);
+      b2 += S;
+    }
+    v0 += bv;
+    w0 += b0;
+    w1 += b1;
+    w2 += b2;
+  }
+
+  // B: this wavefront's 16 rows, in two chains per tile
+  f64x4 acc[8], acd[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) acc[c] = acd[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+  if (pl.mg) {
+    const int Xlo = s * (16 * wave - pl.mg), Xhi = Xlo + 15 * s;
+    const double* fr = ft + cg.FO + Xlo + s * l16 - l4;  // fr[-i]: f(X - (i + l4))
+    int Xc[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int qq = 16 * c + l16;
+      Xc[c] = s * ((qq < r ? qq : r - 1) - pl.mg) - l4;
+    }
+    auto edge = [&](int i0, int steps) {  // cells i0 .. i0 + 4 steps - 1
+      for (int t = 0; t < steps; ++t) {
+        const int i = i0 + 4 * t;
+        const double A = fr[-i];
+        if (t & 1) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const int dd = i - Xc[c];
+            acd[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, sc[dd < 0 ? -dd : dd], acd[c], 0, 0, 0);
+          }
+        } else {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            const int dd = i - Xc[c];
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(A, sc[dd < 0 ? -dd : dd], acc[c], 0, 0, 0);
+          }
+        }
+      }
+    };
+    if (16 * wave < r) {
+      const int left = min(pl.E, pl.E - Xlo);  // cells -left .. -1 reach these rows
+      if (left > 0) edge(-4 * ((left + 3) / 4), (left + 3) / 4);
+      const int right = min(pl.E, Xhi + pl.E + 1 - M);  // cells M .. M + right - 1
+      if (right > 0) edge(M, (right + 3) / 4);
+    }
+  }
+  // B and W's first rows into LDS, over the preparation's arrays
+  double bv[8][4];
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int p = 16 * wave + 4 * k + l4, qq = 16 * c + l16, d = s * (p - qq);
+      double v = 0.0;
+      if (p < r && qq < r) {
+        v = d >= -pl.E && d <= pl.E ? (double)s * ft[cg.FO + d] : 0.0;
+        if (p - qq == k1) v = gur;
+        if (qq - p == k1) v = gdr;
+        if (p - qq == k3 || qq - p == k3) v += rest;
+        v -= acc[c][k] + acd[c][k];
+      }
+      bv[c][k] = v;
+    }
+  __syncthreads();
+  double* P = sh;
+  double* W = sh + kOffW;
+  double* V = sh + kOffV;
+  // (the four parts' sums through P's region first)
+  P[tid] = v0;
+  P[512 + tid] = w0;
+  P[1024 + tid] = w1;
+  P[1536 + tid] = w2;
+  __syncthreads();
+  if (tid < 512) {
+    const int kind = tid >> 7;  // v, up, lo, total
+    const double* x = P + 512 * kind + q;
+    const double v = q < r ? ((x[0] + x[128]) + (x[256] + x[384])) : 0.0;
+    if (kind == 0) V[seg_at(q)] = v;
+    else W[mat_at(kind - 1, q)] = v;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) P[mat_at(16 * wave + 4 * k + l4, 16 * c + l16)] = bv[c][k];
+  __syncthreads();
+
+  // Four squarings; W's rows double beside them.  A plain product would round
+  // each entry of magnitude 0.1 some twenty times, a systematic error of every
+  // later step: the factors are split at 2^-26, so that the products of the
+  // upper parts add up exactly (multiples of 2^-52 below 2) and the rest, 2^27
+  // times smaller, is added once.
+  auto upper = [](double x) { return (x + 0x1.8p26) - 0x1.8p26; };
+  const int ksteps = 4 * ((r + 15) / 16);
+  f64x4 wa[2];
+#pragma unroll 1
+  for (int lv = 0; lv < 4; ++lv) {
+    const int rows = 3 << lv;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) acc[c] = acd[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+    wa[0] = wa[1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    const int rw0 = min(l16, rows - 1), rw1 = min(16 + l16, rows - 1);
+    if (16 * wave < r) {
+#pragma unroll 1
+      for (int t = 0; t < ksteps; ++t) {
+        const int kk = 4 * t + l4;
+        const double A = P[mat_at(16 * wave + l16, kk)], Bw = P[mat_at(kk, 16 * wave + l16)];
+        const double Ah = upper(A), Al = A - Ah;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          if (16 * c < r) {
+            const double Bc = P[mat_at(kk, 16 * c + l16)], Bh = upper(Bc);
+            acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ah, Bh, acc[c], 0, 0, 0);
+            acd[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(Ah, Bc - Bh, acd[c], 0, 0, 0);
+            acd[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(Al, Bc, acd[c], 0, 0, 0);
+          }
+        }
+        wa[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(W[mat_at(rw0, kk)], Bw, wa[0], 0, 0, 0);
+        if (rows > 16) wa[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(W[mat_at(rw1, kk)], Bw, wa[1], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) P[mat_at(16 * wave + 4 * k + l4, 16 * c + l16)] = acc[c][k] + acd[c][k];
+    if (lv < 3) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int row = 4 * k + l4;
+        if (row < rows) W[mat_at(rows + row, 16 * wave + l16)] = wa[0][k];
+      }
+    }
+    __syncthreads();
+  }
+  // B^16 and W into registers: eight threads per row, thread (slot, seg) holding
+  // columns 16 seg .. 16 seg + 15 of B^16's rows slot and slot + 64 and of W's
+  // row slot (three rows for each read of the samples, which LDS reads bound
+  // otherwise).
+  double Pr[2][16], Wr[16];
+  const int slot = tid >> 3, seg = tid & 7;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    Pr[0][k] = P[mat_at(slot, 16 * seg + k)];
+    Pr[1][k] = P[mat_at(slot + 64, 16 * seg + k)];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {  // W's last 24 rows, over B's region
+    const int row = 4 * k + l4;
+    P[mat_at(row, 16 * wave + l16)] = wa[0][k];
+    if (16 + row < kWRows / 2) P[mat_at(16 + row, 16 * wave + l16)] = wa[1][k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int row = slot < kWRows / 2 ? slot : slot - kWRows / 2;
+    Wr[k] = slot < kWRows ? (slot < kWRows / 2 ? W : P)[mat_at(row, 16 * seg + k)] : 0.0;
+  }
+  __syncthreads();
+  // Passes of 16 steps.  Their outputs collect in LDS over B's region and leave
+  // it together: a store to HBM in a pass would be waited for at its barrier.
+  double* O = sh;  // [kRing][48]
+  const int vo = kVSeg * (seg >> 1) + 16 * (seg & 1);
+  int par = 0, pass = 0, n0 = pl.direct + 1;  // n0: the ring's first step
+  for (;;) {
+    const double* v = V + par * 4 * kVSeg + vo;
+    double y0 = 0.0, y1 = 0.0, o1 = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double x = v[k];
+      y0 = fma(Pr[0][k], x, y0);
+      y1 = fma(Pr[1][k], x, y1);
+      o1 = fma(Wr[k], x, o1);
+    }
+    auto sum8 = [](double x) {
+      x += partner<0>(x);
+      x += partner<1>(x);
+      return x + partner<2>(x);
+    };
+    y0 = sum8(y0);
+    y1 = sum8(y1);
+    o1 = sum8(o1);
+    if (seg == 0) {
+      double* vn = V + (par ^ 1) * 4 * kVSeg;
+      vn[seg_at(slot)] = y0;
+      vn[seg_at(slot + 64)] = y1;
+      if (slot < kWRows) O[pass * kWRows + slot] = o1;
+    }
+    __syncthreads();
+    par ^= 1;
+    // the first of the pass's steps whose mass is below tol
+    const uint64_t below =
+        __builtin_amdgcn_ballot_w64(O[pass * kWRows + 3 * (lane & 15) + 2] < a.tol) & 0xFFFFull;
+    const int stop = below ? (int)__builtin_ctzll(below) : kCoarsePow;
+    const int end = min(N, n0 + pass * kCoarsePow + stop);  // steps before this one have outputs
+    const bool last = stop < kCoarsePow || end >= N;
+    if (!last && ++pass < kRing) continue;
+    for (int x = n0 + tid; x < end; x += kCoarseThreads) {
+      const double* o = O + 3 * (x - n0);  // rows of a pass follow each other by step
+      out_up[x] = o[0];
+      out_lo[x] = o[1];
+    }
+    if (last) {
+      for (int x = end + tid; x < N; x += kCoarseThreads) {
+        out_up[x] = 0.0;
+        out_lo[x] = 0.0;
+      }
+      return;
+    }
+    __syncthreads();
+    n0 += kRing * kCoarsePow;
+    pass = 0;
+  }
+}
+
 // MAXT: workgroup size bound; REGD: diagonals per wavefront whose kernel
 // fragments stay in registers (at two wavefronts per SIMD a wavefront's 256
 // registers hold 24 diagonals' fragments beside the rest, at three 12;
@@ -138,6 +676,7 @@ __global__ __launch_bounds__(MAXT) void ddm_density_kernel(DensityArgs a) {
   const double as = drift * a.dt, b = a.b, th = a.thresh, h = (2.0 * th) / (double)M;
   double* out_lo = a.out + (s * 2u) * a.max_steps;  // choice 0: lower bound
   double* out_up = out_lo + a.max_steps;             // choice 1: upper bound
+  if (a.coarse && coarse_plan(a.cells, th, b, as, a.start).ok) return;  // the coarse kernel's setting
 
   if (tid == 0) {
     band[0] = 0x7FFFFFFF;
@@ -372,6 +911,8 @@ __global__ __launch_bounds__(MAXT) void ddm_density_kernel(DensityArgs a) {
 
 }  // namespace
 
+size_t coarse_lds_bytes() { return kCoarseLds * sizeof(double); }
+
 // LDS: the kernel row, two zero-padded mass vectors, the partial sums and
 // the window's row sums.
 size_t density_lds_bytes(uint32_t cells) {
@@ -380,10 +921,26 @@ size_t density_lds_bytes(uint32_t cells) {
           (size_t)kWin * 3u * (g.W * 64u / 16u)) * sizeof(double);
 }
 
-hipError_t launch_ddm_density(const DensityArgs& a, hipStream_t st) {
-  const DensityGeo g = density_geo(a.cells);
-  if (a.cells < 16u || g.W * 64u > (uint32_t)kMaxThreads || 2u * g.W * 64u < 256u * g.NT)
+// Fewer steps than this cost less on the full grid than the coarse form's
+// preparation does (0.3 ms; a full-grid step costs 1.7 us at 120 cells, 2.3 at
+// 333, 3.8 at 537, 6.8 at 1000).
+constexpr uint32_t kCoarseSteps = 192;
+
+hipError_t launch_ddm_density(const DensityArgs& args, hipStream_t st) {
+  const DensityGeo g = density_geo(args.cells);
+  if (args.cells < 16u || g.W * 64u > (uint32_t)kMaxThreads || 2u * g.W * 64u < 256u * g.NT)
     return hipErrorInvalidValue;
+  // Which form a setting takes depends on its drift: known here without a
+  // grid, else both kernels run and each leaves the other's settings alone.
+  DensityArgs a = args;
+  const CoarsePlan p = coarse_plan(a.cells, a.thresh, a.b, a.n_signals ? 0.0 : a.drift * a.dt, a.start);
+  a.coarse = args.coarse && p.ok && a.max_steps >= kCoarseSteps;
+  if (a.coarse) {
+    hipLaunchKernelGGL(ddm_density_coarse_kernel, dim3((uint32_t)a.n_settings), dim3(kCoarseThreads),
+                       coarse_lds_bytes(), st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !a.n_signals) return e;
+  }
   if (g.NT == 4u)
     hipLaunchKernelGGL((ddm_density_kernel<768, 12>), dim3((uint32_t)a.n_settings), dim3(g.W * 64u),
                        density_lds_bytes(a.cells), st, a);

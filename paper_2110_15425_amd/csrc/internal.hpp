@@ -236,6 +236,8 @@ struct DensityArgs {
   uint64_t n_settings;
   uint32_t max_steps, cells, n_signals;
   double dt, drift, b, thresh, start, tol;
+  uint32_t coarse;  // to the launcher: the device has the coarse form's LDS; to the
+                    // full-grid kernel: settings that the coarse form takes are left to it
   const double* grid;
   double* out;  // [settings][2][max_steps]
 };
@@ -273,5 +275,6 @@ hipError_t launch_uf_step(const UnfusedArgs& a, int precision, uint32_t n, int c
 hipError_t launch_uf_reduce(const UnfusedArgs& a, hipStream_t st);
 hipError_t launch_ddm_density(const DensityArgs& a, hipStream_t st);
 size_t density_lds_bytes(uint32_t cells);
+size_t coarse_lds_bytes();
 
 }  // namespace cm
