@@ -618,6 +618,7 @@ void fill_prep(const cm_model* m, const cm_sweep* s, const cm_result* r, char* w
     it.d.drive = (double*)(ws + L.drive);
     it.d.correct = (int32_t*)(ws + L.correct);
     it.d.norm2 = (double*)(ws + L.norm2);
+    it.d.dt = m->precision == CM_FP32_STEP ? p[CM_LCA_DT] : 0.0;
     tables = 9 + it.d.n_settings * 9u;
   }
   it.end = (b.n ? b.it[b.n - 1].end : 0) + it.n_hist + it.n_stats + it.n_extra + tables;
@@ -723,8 +724,9 @@ cm_status launch_loop_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, 
   a.leak = p[CM_LCA_LEAK];
   a.comp = p[CM_LCA_COMP];
   a.cost = p[CM_LOOP_COST];
+  a.pf = cm::lca_f32(a.leak, a.comp, a.dt, a.b);
   a.grid = s->grid;
-  a.drive = (const double*)(ws + L.drive);
+  a.drive = ws + L.drive;
   a.norm2 = (const double*)(ws + L.norm2);
   a.correct = (const int32_t*)(ws + L.correct);
   a.hist = r->hist;
@@ -736,15 +738,22 @@ cm_status launch_loop_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, 
   cm_status st = enqueue_prep(m, s, r, ws, L, stream);
   if (st != CM_OK) return st;
   const uint32_t team = cm::loop_team_lanes(a.J, a.total_runs, (uint32_t)h->cu_count);
-  const uint64_t teams_per_block = 256u / team;
-  const uint64_t want = (a.total_runs + teams_per_block - 1) / teams_per_block;
-  // Teams take runs in a fixed stride, so a workgroup's work varies with its
-  // runs' lengths; with several rounds of workgroups the dispatcher refills
-  // freed slots and evens that out (measured on MI355X: wavefront teams 10 %
-  // faster at 32 workgroups per CU than at 8, one run per team slower;
-  // workgroup teams best at 8)
-  const uint64_t per_cu = team == 256u ? 8u : 32u;
-  const uint32_t blocks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, per_cu * h->cu_count));
+  // Workgroups take consecutive runs, so that they count them in a window in
+  // LDS; with several rounds of workgroups the dispatcher refills freed slots and
+  // evens out their uneven lengths (measured on MI355X, 80,000 runs of 64
+  // allocations x 4 samples, 4 / 8 / 16 / 32 workgroups per compute unit: 1322 /
+  // 1178 / 1098 / 1080 us).
+  const uint64_t teams = 256u / team, per_cu = team == 256u ? 8u : 32u;
+  a.chunk = std::max<uint64_t>(teams, (a.total_runs + per_cu * h->cu_count - 1) / (per_cu * h->cu_count));
+  a.chunk = std::min<uint64_t>((a.chunk + teams - 1) / teams * teams, kMaxChunk);
+  a.trials_magic = cm::udiv_magic_for((uint32_t)s->trials);
+  const size_t rec_bytes = 4u * cm::rec_words(a.n_bins);
+  const uint64_t window = std::min<uint64_t>((a.chunk - 1) / a.trials + 2, a.n_settings);
+  a.direct = window * rec_bytes > kLdsBudget;
+  a.window = a.direct ? 0u : (uint32_t)window;
+  const uint64_t groups = (a.total_runs + a.chunk - 1) / a.chunk;
+  if (groups > 0x7FFFFFFFull) return fail(CM_E_INVALID, "too many runs for one launch");
+  const uint32_t blocks = (uint32_t)groups;
   hipError_t e;
   ProfScope prof{h, stream, timed};
   if ((e = prof.begin()) != hipSuccess) return hip_fail(e, "hipEventRecord");

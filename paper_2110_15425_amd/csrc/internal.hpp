@@ -92,7 +92,8 @@ struct DriveArgs {
   double gain, bias, offset;
   const double* weights;
   const double* grid;
-  double* drive;     // [settings][9][2]
+  double* drive;     // [settings][9][2]; closed loop: [9][allocations][2]
+  double dt;         // closed loop in FP32 steps: the entries are float(I dt), else 0
   int32_t* correct;  // [9]
   double* norm2;     // closed loop: [allocations] c_A^2 + c_B^2, else NULL
 };
@@ -216,11 +217,14 @@ struct UnfusedArgs {
 // Arguments of the closed-loop control kernel.
 struct LoopArgs {
   uint64_t trials, n_settings, total_runs, seed;
-  uint64_t steps_magic;
+  uint64_t steps_magic, trials_magic;
+  uint64_t chunk;            // runs handed to one workgroup
+  uint32_t direct, window;   // as SimArgs
   uint32_t max_steps, n_bins, n_signals, L, J, M, nonneg, pad;
   double thresh, flag_eps, b, dt, leak, comp, cost;
+  LcaF32 pf;  // FP32 steps: float(leak dt), float(comp dt), float(b)
   const double* grid;      // [n_settings] control-cost weights, or NULL
-  const double* drive;     // [J][9][2]
+  const void* drive;       // [9][J][2]: I in double (FP64) or float(I dt) (FP32 steps)
   const double* norm2;     // [J] c_A^2 + c_B^2 of allocation j
   const int32_t* correct;  // [9]
   uint64_t* hist;

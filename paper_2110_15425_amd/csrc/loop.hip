@@ -17,28 +17,31 @@
 // allocations, over too few runs to fill the GPU with wavefront teams, takes
 // the whole workgroup (P = 256).  Lane i of the team evaluates allocations
 // i, i + P, ... with all their samples (four at a time when it has several,
-// so that independent random-number chains overlap).  A wavefront team finds
-// the best score by one minimum over the wavefront, the winner by a ballot of
-// the lanes at it (exact ties, rare, by the smallest (priority, allocation)),
-// and the second-best score by a second minimum; smaller teams use a
-// butterfly of (score, second score, allocation) cross-lane moves (DPP within
-// 16-lane rows, shuffles across them), and P = 256 adds a fold of the four
-// wavefronts' results through LDS.  Every lane of the team then applies the
-// chosen step to its own copy of the state (identical arithmetic, identical
-// bits), so the team never broadcasts and its control flow stays uniform; a
-// wavefront team draws the normals of its run's own steps 64 at a time, one
-// step per lane, and reads each step's from its lane.  Teams take runs in a
-// fixed stride, and a finished run
-// is counted straight into global memory by the team's first lane: a run
-// costs L^2 M look-ahead steps per step, so the atomics are negligible.  The
-// allocation drive table [L^2][9][2] and the allocations' squared norms
+// so that independent random-number chains overlap).  A wavefront team
+// (loop_wave_kernel) finds the best score through its float image; the other
+// teams (loop_kernel) use a butterfly of (score, second score, allocation)
+// cross-lane moves (DPP within 16-lane rows, shuffles across them), and P = 256
+// adds a fold of the four wavefronts' results through LDS.  Every lane of the
+// team then applies the chosen step to its own copy of the state (identical
+// arithmetic, identical bits), so the team never broadcasts and its control flow
+// stays uniform; a wavefront team draws the normals of its run's own steps 64 at
+// a time, one step per lane, and reads each step's from its lane.  A workgroup
+// takes consecutive runs and counts them in an LDS window: counted one by one in
+// global memory, the runs of a few settings wait for each other's atomics.  The
+// allocation drive table [9][L^2][2] and the allocations' squared norms
 // c_A^2 + c_B^2 [L^2] are computed once per sweep by the preparation kernel.
+//
+// Measured on MI355X, 80,000 runs over 4 settings, against a global count, a
+// [L^2][9][2] table and double minima: L = 8, M = 4 in FP32 steps 1.95 to 1.05
+// ms, in FP64 3.87 to 1.73 (half of that from the normals' table); L = 2, M = 4
+// 1.61 to 0.19 ms; L = 100, M = 1 (1,000 runs) 2.85 to 2.26 ms.
 #include <type_traits>
 
 #include "internal.hpp"
 #include "lca_step.hpp"
 #include "normal64.hpp"
 #include "rng.hpp"
+#include "window.hpp"
 
 namespace cm {
 namespace {
@@ -99,39 +102,44 @@ __device__ __forceinline__ Words philox_stream(const StreamKey& r, uint32_t c3, 
 constexpr uint32_t kStreamPick = 0xC0000000u;  // | allocation
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 
-// One LCA step in the model's precision from its normals (z0, z1 in FP64;
-// zf0, zf1 in FP32 steps, with idt_i = float(I_i dt)): the arithmetic of the
-// open-loop LCA kernel, so that a one-allocation loop reproduces it bit for
-// bit.
+// An allocation's drive of both units for one stimulus: I_i in FP64,
+// float(I_i dt) in FP32 steps.  The table is [stimulus][allocation], so that a
+// wavefront's lanes read consecutive entries.
 template <int PREC>
-__device__ __forceinline__ void lca_update(const LoopArgs& a, double x0, double x1, double in0,
-                                           double in1, float idt0, float idt1, double z0, double z1,
-                                           float zf0, float zf1, double& y0, double& y1) {
-  if (PREC == CM_FP64) {
-    y0 = lca_next_f64(x0, x1, in0, a.leak, a.comp, a.dt, a.b, z0);
-    y1 = lca_next_f64(x1, x0, in1, a.leak, a.comp, a.dt, a.b, z1);
+struct Drive {
+  typename std::conditional<PREC == CM_FP64, double, float>::type a, b;
+};
+template <int PREC>
+__device__ __forceinline__ const Drive<PREC>* drive_of(const LoopArgs& a, uint32_t stim) {
+  return (const Drive<PREC>*)a.drive + (uint64_t)stim * a.J;
+}
+
+// One LCA step in the model's precision from its normals or a random block: the
+// arithmetic of the open-loop LCA kernel, so that a one-allocation loop
+// reproduces it bit for bit.
+template <int PREC, class Z>
+__device__ __forceinline__ void lca_update(const LoopArgs& a, double x0, double x1, const Drive<PREC>& d, Z z0,
+                                           Z z1, double& y0, double& y1) {
+  if constexpr (PREC == CM_FP64) {
+    y0 = lca_next_f64(x0, x1, d.a, a.leak, a.comp, a.dt, a.b, z0);
+    y1 = lca_next_f64(x1, x0, d.b, a.leak, a.comp, a.dt, a.b, z1);
   } else {
-    const LcaF32 pf = lca_f32(a.leak, a.comp, a.dt, a.b);
     const float xf0 = (float)x0, xf1 = (float)x1;
-    y0 = x0 + (double)lca_inc_f32(pf, idt0, xf0, xf1, zf0);
-    y1 = x1 + (double)lca_inc_f32(pf, idt1, xf1, xf0, zf1);
+    y0 = x0 + (double)lca_inc_f32(a.pf, d.a, xf0, xf1, z0);
+    y1 = x1 + (double)lca_inc_f32(a.pf, d.b, xf1, xf0, z1);
   }
   if (a.nonneg) {
     if (y0 < 0.0) y0 = 0.0;
     if (y1 < 0.0) y1 = 0.0;
   }
 }
-
-// The same step from a random block.
 template <int PREC>
-__device__ __forceinline__ void lca_step(const LoopArgs& a, double x0, double x1, double in0,
-                                         double in1, float idt0, float idt1, const Words& w,
-                                         const NormTab* nt, double& y0, double& y1) {
-  double z0 = 0.0, z1 = 0.0;
-  float zf0 = 0.0f, zf1 = 0.0f;
-  if (PREC == CM_FP64) normals64(w, *nt, z0, z1);
-  else normals32(w, zf0, zf1);
-  lca_update<PREC>(a, x0, x1, in0, in1, idt0, idt1, z0, z1, zf0, zf1, y0, y1);
+__device__ __forceinline__ void lca_step(const LoopArgs& a, double x0, double x1, const Drive<PREC>& d,
+                                         const Words& w, const NormTab* nt, double& y0, double& y1) {
+  decltype(d.a + d.a) z0, z1;
+  if constexpr (PREC == CM_FP64) normals64(w, *nt, z0, z1);
+  else normals32(w, z0, z1);
+  lca_update<PREC>(a, x0, x1, d, z0, z1, y0, y1);
 }
 
 // Tie rule among allocations with equal scores: the smaller (Philox priority,
@@ -224,6 +232,17 @@ __device__ __forceinline__ double wave_min(double v) {
   v = halves_min<4>(v);
   return halves_min<5>(v);
 }
+__device__ __forceinline__ float wave_min_f32(float v) {
+  v = fminf(v, __uint_as_float(partner<0>(__float_as_uint(v))));
+  v = fminf(v, __uint_as_float(partner<1>(__float_as_uint(v))));
+  v = fminf(v, __uint_as_float(partner<2>(__float_as_uint(v))));
+  v = fminf(v, __uint_as_float(partner<3>(__float_as_uint(v))));
+  uint32_t p, q;
+  halves<4>(__float_as_uint(v), p, q);
+  v = fminf(__uint_as_float(p), __uint_as_float(q));
+  halves<5>(__float_as_uint(v), p, q);
+  return fminf(__uint_as_float(p), __uint_as_float(q));
+}
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
   auto step = [&](auto round) {
     constexpr int R = decltype(round)::value;
@@ -238,6 +257,209 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
   return halves_min<5>(v);
 }
 
+// A workgroup's runs: chunk consecutive ones (the first of setting s_lo), counted
+// in the LDS window; its teams take them in turn.
+struct Chunk {
+  uint32_t* lds;
+  uint32_t len, s_lo, t_lo;
+  __device__ __forceinline__ explicit Chunk(const LoopArgs& a) {
+    extern __shared__ unsigned long long lds_u64[];
+    lds = (uint32_t*)lds_u64;
+    const uint64_t r0 = (uint64_t)blockIdx.x * a.chunk;
+    len = (uint32_t)min(a.chunk, a.total_runs - r0);
+    s_lo = (uint32_t)(r0 / a.trials);
+    t_lo = (uint32_t)(r0 - (uint64_t)s_lo * a.trials);
+    for (uint32_t i = threadIdx.x; i < a.window * rec_words(a.n_bins); i += blockDim.x) lds[i] = 0u;
+    __syncthreads();
+  }
+  __device__ __forceinline__ void run(const LoopArgs& a, uint32_t off, uint32_t& s, uint32_t& t) const {
+    const uint32_t local = t_lo + off;  // < 2^31 + chunk
+    s = s_lo + udiv_magic(local, a.trials_magic);
+    t = local - (s - s_lo) * (uint32_t)a.trials;
+  }
+  __device__ __forceinline__ void flush(const LoopArgs& a) const {
+    __syncthreads();
+    if (!a.direct) flush_window(a, lds, s_lo);
+  }
+};
+
+// A wavefront per run (17 allocations and more).  Everything that belongs to
+// the run -- its step, state, correct response, the key of the step's look-ahead
+// blocks, the chosen allocation -- is the same in every lane and lives in
+// scalar registers or branches as far as the hardware has them.
+// ONE: at most one allocation per lane (J <= 64), whose score needs no scan;
+// else lanes take allocations lane, lane + 64, ..., U at a time.
+//
+// Bound by VALU issue (1,380 cycles a wavefront-step at L = 8, M = 4, about 340
+// instructions).  The best score is found through its float image, six
+// single-instruction rounds instead of six of three on doubles: rounding is
+// monotone, so the lanes at the smallest image hold the best score, and nearly
+// always there is one such lane; a tie of images goes through the doubles.
+// Whether another score comes within eps of the best takes one comparison per
+// lane, not a second minimum.
+template <int PREC, int U, bool ONE>
+__global__ __launch_bounds__(kLoopBlock) void loop_wave_kernel(LoopArgs a) {
+  __shared__ NormLds<PREC> norm;
+  norm.load();
+  __syncthreads();
+  const NormTab* nt = norm.get();
+  constexpr uint32_t kTeams = kLoopBlock / 64;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t team = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint32_t J = a.J, M = a.M, N = a.max_steps;
+  const double th = a.thresh, eps = a.flag_eps, guard = th - 2.0 * eps;
+  const bool pow2 = (M & (M - 1u)) == 0u;  // the mean is then a product with 1 / M, exactly
+  const double inv_m = 1.0 / (double)M;
+  Chunk ch(a);
+  for (uint32_t off = team; off < ch.len; off += kTeams) {
+    uint32_t s, t;
+    ch.run(a, off, s, t);
+    const uint32_t stim = t % 9u;
+    const int c = __builtin_amdgcn_readfirstlane(a.correct[stim]);
+    const double kappa = a.n_signals ? a.grid[s] : a.cost;
+    const Drive<PREC>* drive = drive_of<PREC>(a, stim);
+    double x0 = 0.0, x1 = 0.0;
+    bool flag = false;
+    int choice = -1;
+    // the run's own normals for steps 64 b .. 64 b + 63, lane i holding step
+    // 64 b + i's (drawn when step 64 b comes up, read back by lane each step)
+    double ez0 = 0.0, ez1 = 0.0;
+    float ef0 = 0.0f, ef1 = 0.0f;
+    uint32_t n = 1;
+    for (; n <= N; ++n) {
+      const uint32_t k = n - 1u;
+      if ((k & 63u) == 0u) {
+        const Words w = philox(k + lane, t, s, 0u, k0, k1);
+        if constexpr (PREC == CM_FP64) normals64(w, *nt, ez0, ez1);
+        else normals32(w, ef0, ef1);
+      }
+      const StreamKey sk = stream_key(k, t, s, k0, k1);
+      double bv = INFINITY, sv = INFINITY;
+      uint32_t bj = kNone;
+      // The search for correct response C: look-aheads of allocations
+      // j, j + 64, ... (U of them), scored in allocation order.
+      auto search = [&](auto correct) {
+        constexpr bool C = decltype(correct)::value;
+        const double dx = C ? x1 - x0 : x0 - x1;  // x_c - x_w
+        for (uint32_t jb = 0; jb < J; jb += U * 64u) {  // the same trips in every lane
+          const uint32_t j = jb + lane;
+          double gs[U];
+          Drive<PREC> in[U];
+          uint32_t ju[U];
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) {
+            ju[u] = min(j + u * 64u, J - 1u);  // slots past J repeat the last one and are discarded
+            in[u] = drive[ju[u]];
+            gs[u] = 0.0;
+          }
+          for (uint32_t m = 0; m < M; ++m) {
+#pragma unroll
+            for (uint32_t u = 0; u < U; ++u) {
+              const Words w = philox_stream(sk, kStreamLook | (ju[u] * M + m), k0, k1);
+              double y0, y1;
+              lca_step<PREC>(a, x0, x1, in[u], w, nt, y0, y1);
+              gs[u] = gs[u] + ((C ? y1 - y0 : y0 - y1) - dx);
+            }
+          }
+#pragma unroll
+          for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t jj = ju[u];
+            const bool real = j + u * 64u < J;
+            double mean;
+            if (pow2) {
+              mean = gs[u] * inv_m;
+            } else {
+              // a branch of its own: the division is not evaluated beside the
+              // product when M is a power of two
+              asm volatile("" ::: "memory");
+              mean = gs[u] / (double)M;
+            }
+            const double V = kappa * a.norm2[jj] - mean;
+            if constexpr (ONE) {
+              if (real && V == V) {
+                bv = V;
+                bj = jj;
+              }
+            } else if (!real) {
+            } else if (V < bv) {
+              sv = bv;
+              bv = V;
+              bj = jj;
+            } else if (V == bv) {
+              sv = V;
+              if (tie_wins(jj, bj, k, t, s, k0, k1)) bj = jj;
+            } else if (V < sv) {
+              sv = V;
+            }
+          }
+        }
+      };
+      if (c) search(std::true_type{});
+      else search(std::false_type{});
+      // The best score over the wavefront; an exact tie anywhere (several lanes
+      // at it, or a lane holding two allocations at it) goes to the smallest
+      // (priority, allocation), else the one lane at it holds the winner.
+      const float f = (float)bv;
+      uint64_t at = __builtin_amdgcn_ballot_w64(f == wave_min_f32(f));
+      uint32_t pick;
+      bool tie = true;
+      if (__builtin_expect(__popcll(at) == 1, 1)) {
+        const int l = (int)__builtin_ctzll(at);
+        const double gb = read_lane(bv, l);
+        pick = (uint32_t)__builtin_amdgcn_readlane((int)bj, l);
+        const double other = lane == (uint32_t)l ? sv : bv;  // the scores beside the best
+        tie = !ONE && __builtin_amdgcn_ballot_w64(other == gb) != 0;
+        if (!tie && __builtin_amdgcn_ballot_w64(other - gb < eps) != 0) flag = true;
+      }
+      if (__builtin_expect(tie, 0)) {
+        const double gb = wave_min(bv);
+        at = __builtin_amdgcn_ballot_w64(bv == gb);
+        tie = __popcll(at) != 1 || __builtin_amdgcn_ballot_w64(sv == gb) != 0;
+        if (tie) {
+          uint64_t key = ~0ull;
+          if (bv == gb && bj != kNone)
+            key = ((uint64_t)philox(k, t, s, kStreamPick | bj, k0, k1).w0 << 32) | bj;
+          pick = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)wave_min_u64(key));
+        } else {
+          const int l = (int)__builtin_ctzll(at);
+          pick = (uint32_t)__builtin_amdgcn_readlane((int)bj, l);
+          const double other = lane == (uint32_t)l ? sv : bv;
+          if (__builtin_amdgcn_ballot_w64(other - gb < eps) != 0) flag = true;
+        }
+      }
+      // the step itself, with the chosen allocation, on the run's own stream
+      // (allocation 0 if no score compared as a number)
+      const Drive<PREC> d = drive[pick == kNone ? 0u : pick];
+      const int src = (int)(k & 63u);
+      double y0, y1;
+      if constexpr (PREC == CM_FP64)
+        lca_update<PREC>(a, x0, x1, d, read_lane(ez0, src), read_lane(ez1, src), y0, y1);
+      else
+        lca_update<PREC>(a, x0, x1, d, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ef0), src)),
+                         __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ef1), src)), y0, y1);
+      x0 = y0;
+      x1 = y1;
+      // the exact tests only near the threshold
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(x0 >= guard || x1 >= guard) != 0, 0)) {
+        if (__builtin_amdgcn_ballot_w64(fabs(x0 - th) < eps || fabs(x1 - th) < eps) != 0) flag = true;
+        const double mx = x0 > x1 ? x0 : x1;
+        if (__builtin_amdgcn_ballot_w64(mx >= th) != 0) {
+          choice = __builtin_amdgcn_ballot_w64(x1 > x0) != 0 ? 1 : 0;
+          if (__builtin_amdgcn_ballot_w64(fabs(x0 - x1) < eps) != 0) flag = true;
+          break;
+        }
+      }
+    }
+    if (lane == 0) {
+      const double st[2] = {x0, x1};
+      count_run(a, ch.lds, ch.s_lo, s, t, choice >= 0 ? n : N, choice, c, flag, st, 2);
+    }
+  }
+  ch.flush(a);
+}
+
+// Teams of 1, 4 or 16 lanes, or of a whole workgroup (P = 256).
 template <int PREC, int P, int U>
 __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
   // P = kLoopBlock: the whole workgroup is one team; its four wavefronts
@@ -255,18 +477,17 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
   uint32_t folds = 0;
   const uint32_t j0 = P > 64 ? threadIdx.x : (threadIdx.x & 63u) % (uint32_t)P;
   const uint32_t teams_per_block = kLoopBlock / P;
-  const uint64_t n_teams = (uint64_t)gridDim.x * teams_per_block;
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  const uint32_t T = (uint32_t)a.trials, J = a.J, M = a.M, N = a.max_steps;
+  const uint32_t J = a.J, M = a.M, N = a.max_steps;
   const double th = a.thresh, eps = a.flag_eps;
-  // a wavefront-or-wider team's run index is the same in every lane
-  const uint32_t team = P >= 64 ? __builtin_amdgcn_readfirstlane(threadIdx.x / P) : threadIdx.x / P;
-  const uint32_t lane = threadIdx.x & 63u;
-  for (uint64_t run = (uint64_t)blockIdx.x * teams_per_block + team; run < a.total_runs;
-       run += n_teams) {
-    const uint32_t s = (uint32_t)(run / T), t = (uint32_t)(run - (uint64_t)s * T);
+  const uint32_t team = P > 64 ? 0u : threadIdx.x / P;
+  Chunk ch(a);
+  for (uint32_t off = team; off < ch.len; off += teams_per_block) {
+    uint32_t s, t;
+    ch.run(a, off, s, t);
     const uint32_t stim = t % 9u;
     const int c = a.correct[stim];
+    const Drive<PREC>* drive = drive_of<PREC>(a, stim);
     const double kappa = a.n_signals ? a.grid[s] : a.cost;
     // the mean over M samples: a power of two divides exactly as a product
     // with its reciprocal, which saves a division per allocation and step
@@ -275,21 +496,9 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
     double x0 = 0.0, x1 = 0.0;
     bool flag = false;
     int choice = -1;
-    // P = 64: the run's own normals for steps 64 b .. 64 b + 63, lane i
-    // holding step 64 b + i's (drawn when step 64 b comes up, read back by
-    // lane each step: one block per wavefront and 64 steps)
-    double ez0 = 0.0, ez1 = 0.0;
-    float ef0 = 0.0f, ef1 = 0.0f;
     uint32_t n = 1;
     for (; n <= N; ++n) {
       const uint32_t k = n - 1u;
-      if constexpr (P == 64) {
-        if ((k & 63u) == 0u) {
-          const Words w = philox(k + lane, t, s, 0u, k0, k1);
-          if (PREC == CM_FP64) normals64(w, *nt, ez0, ez1);
-          else normals32(w, ef0, ef1);
-        }
-      }
       const double dx = c ? x1 - x0 : x0 - x1;  // x_c - x_w
       // the look-ahead blocks of this step differ only in their stream word
       const StreamKey sk = stream_key(k, t, s, k0, k1);
@@ -301,19 +510,13 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
       // allocation order, as one at a time would.  Slots past J repeat
       // allocation j and are discarded.
       for (uint32_t j = j0; j < J; j += U * P) {
-        double gs[U], i0[U], i1[U];
-        float f0[U], f1[U];
+        double gs[U];
+        Drive<PREC> in[U];
         uint32_t ju[U];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
           ju[u] = j + u * P < J ? j + u * P : j;
-          const double* d = a.drive + ((uint64_t)ju[u] * 9u + stim) * 2u;
-          i0[u] = d[0];
-          i1[u] = d[1];
-          if constexpr (P == 64) {  // rounded once per allocation and step
-            f0[u] = (float)(i0[u] * a.dt);
-            f1[u] = (float)(i1[u] * a.dt);
-          }
+          in[u] = drive[ju[u]];
           gs[u] = 0.0;
         }
         for (uint32_t m = 0; m < M; ++m) {
@@ -321,11 +524,7 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
           for (uint32_t u = 0; u < U; ++u) {
             const Words w = philox_stream(sk, kStreamLook | (ju[u] * M + m), k0, k1);
             double y0, y1;
-            if constexpr (P == 64)
-              lca_step<PREC>(a, x0, x1, i0[u], i1[u], f0[u], f1[u], w, nt, y0, y1);
-            else
-              lca_step<PREC>(a, x0, x1, i0[u], i1[u], (float)(i0[u] * a.dt), (float)(i1[u] * a.dt), w,
-                             nt, y0, y1);
+            lca_step<PREC>(a, x0, x1, in[u], w, nt, y0, y1);
             gs[u] = gs[u] + ((c ? y1 - y0 : y0 - y1) - dx);
           }
         }
@@ -355,34 +554,9 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
           }
         }
       }
-      bool near_pick = false;
-      if constexpr (P == 64) {
-        // The best score over the wavefront; an exact tie anywhere (several
-        // lanes at it, or a lane holding two allocations at it) goes to the
-        // smallest (priority, allocation), else the one lane at it holds the
-        // winner.  The second-lowest score is the winner's own second or
-        // another lane's best; exact ties leave none above the best.
-        const double gb = wave_min(bv);
-        const bool at = bv == gb;
-        const uint64_t tied = __builtin_amdgcn_ballot_w64(at);
-        const bool tie = __popcll(tied) > 1 || __builtin_amdgcn_ballot_w64(sv == gb) != 0;
-        uint32_t pick;
-        if (__builtin_expect(!tie, 1)) {
-          pick = (uint32_t)__builtin_amdgcn_readlane((int)bj, (int)__builtin_ctzll(tied));
-        } else {
-          uint64_t key = ~0ull;
-          if (at && bj != kNone)
-            key = ((uint64_t)philox(k, t, s, kStreamPick | bj, k0, k1).w0 << 32) | bj;
-          pick = (uint32_t)wave_min_u64(key);
-        }
-        const double second = wave_min(at ? sv : bv);
-        near_pick = !tie && second > gb && second - gb < eps;
-        bv = gb;
-        bj = pick;
-      }
       auto join = [&](auto round) {
         constexpr int R = decltype(round)::value;
-        if constexpr (P != 64 && (1 << R) < (P < 64 ? P : 64)) {
+        if constexpr ((1 << R) < (P < 64 ? P : 64)) {
           const double ov = partner<R>(bv), os = partner<R>(sv);
           const uint32_t oj = partner<R>(bj);
           const double ns = fmin(fmin(sv, os), fmax(bv, ov));
@@ -422,28 +596,12 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
           sv = ns;
         }
       }
-      if (P == 64 ? near_pick : (sv > bv && sv - bv < eps)) flag = true;
+      if (sv > bv && sv - bv < eps) flag = true;
       // the step itself, with the chosen allocation, on the run's own stream
       // (allocation 0 if no score compared as a number)
-      const double* d = a.drive + ((uint64_t)(bj == kNone ? 0u : bj) * 9u + stim) * 2u;
-      const double e0 = d[0], e1 = d[1];
-      const float g0 = (float)(e0 * a.dt), g1 = (float)(e1 * a.dt);
+      const Drive<PREC> d = drive[bj == kNone ? 0u : bj];
       double y0, y1;
-      if constexpr (P == 64) {
-        const int src = (int)(k & 63u);
-        double z0 = 0.0, z1 = 0.0;
-        float zf0 = 0.0f, zf1 = 0.0f;
-        if (PREC == CM_FP64) {
-          z0 = read_lane(ez0, src);
-          z1 = read_lane(ez1, src);
-        } else {
-          zf0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ef0), src));
-          zf1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ef1), src));
-        }
-        lca_update<PREC>(a, x0, x1, e0, e1, g0, g1, z0, z1, zf0, zf1, y0, y1);
-      } else {
-        lca_step<PREC>(a, x0, x1, e0, e1, g0, g1, philox(k, t, s, 0u, k0, k1), nt, y0, y1);
-      }
+      lca_step<PREC>(a, x0, x1, d, philox(k, t, s, 0u, k0, k1), nt, y0, y1);
       x0 = y0;
       x1 = y1;
       if (fabs(x0 - th) < eps || fabs(x1 - th) < eps) flag = true;
@@ -455,48 +613,31 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
       }
     }
     if (j0 == 0) {
-      const uint32_t steps = choice >= 0 ? n : N;
-      uint64_t* st = a.stats + (uint64_t)s * CM_NSTAT;
-      if (choice >= 0) {
-        const uint32_t bin = udiv_magic((steps - 1u) * a.n_bins, a.steps_magic);
-        atomicAdd((unsigned long long*)&a.hist[((uint64_t)s * 2u + choice) * a.n_bins + bin], 1ull);
-        atomicAdd((unsigned long long*)&st[CM_ST_DEC0 + choice], 1ull);
-        atomicAdd((unsigned long long*)&st[CM_ST_SUMN0 + choice], (unsigned long long)steps);
-        atomicAdd((unsigned long long*)&st[CM_ST_SUMSQ0 + choice],
-                  (unsigned long long)steps * (unsigned long long)steps);
-        if (choice == c) atomicAdd((unsigned long long*)&st[CM_ST_CORRECT], 1ull);
-      } else {
-        atomicAdd((unsigned long long*)&st[CM_ST_UNDEC], 1ull);
-      }
-      if (flag) atomicAdd((unsigned long long*)&st[CM_ST_FLAGGED], 1ull);
-      if (a.run_choice) {
-        a.run_choice[run] = (int8_t)choice;
-        a.run_step[run] = steps;
-        a.run_flag[run] = flag ? 1 : 0;
-        if (a.run_state) {
-          a.run_state[run * 2u] = x0;
-          a.run_state[run * 2u + 1u] = x1;
-        }
-      }
+      const double st[2] = {x0, x1};
+      count_run(a, ch.lds, ch.s_lo, s, t, choice >= 0 ? n : N, choice, c, flag, st, 2);
     }
   }
+  ch.flush(a);
 }
 
 template <int PREC>
 hipError_t launch_prec(const LoopArgs& a, uint32_t team, uint32_t blocks, hipStream_t st) {
+  const size_t lds = (size_t)a.window * rec_words(a.n_bins) * 4u;
   if (team == kLoopBlock)
-    hipLaunchKernelGGL((loop_kernel<PREC, kLoopBlock, kLoopChains>), dim3(blocks), dim3(kLoopBlock), 0,
+    hipLaunchKernelGGL((loop_kernel<PREC, kLoopBlock, kLoopChains>), dim3(blocks), dim3(kLoopBlock), lds,
                        st, a);
   else if (a.J == 1)
-    hipLaunchKernelGGL((loop_kernel<PREC, 1, 1>), dim3(blocks), dim3(kLoopBlock), 0, st, a);
+    hipLaunchKernelGGL((loop_kernel<PREC, 1, 1>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
   else if (a.J <= 4)
-    hipLaunchKernelGGL((loop_kernel<PREC, 4, 1>), dim3(blocks), dim3(kLoopBlock), 0, st, a);
+    hipLaunchKernelGGL((loop_kernel<PREC, 4, 1>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
   else if (a.J <= 16)
-    hipLaunchKernelGGL((loop_kernel<PREC, 16, 1>), dim3(blocks), dim3(kLoopBlock), 0, st, a);
+    hipLaunchKernelGGL((loop_kernel<PREC, 16, 1>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
+  else if (a.J <= 64)
+    hipLaunchKernelGGL((loop_wave_kernel<PREC, 1, true>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
   else if (a.J < 4u * 64u)  // fewer than four allocations per lane
-    hipLaunchKernelGGL((loop_kernel<PREC, 64, 1>), dim3(blocks), dim3(kLoopBlock), 0, st, a);
+    hipLaunchKernelGGL((loop_wave_kernel<PREC, 1, false>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
   else
-    hipLaunchKernelGGL((loop_kernel<PREC, 64, kLoopChains>), dim3(blocks), dim3(kLoopBlock), 0, st, a);
+    hipLaunchKernelGGL((loop_wave_kernel<PREC, kLoopChains, false>), dim3(blocks), dim3(kLoopBlock), lds, st, a);
   return hipGetLastError();
 }
 

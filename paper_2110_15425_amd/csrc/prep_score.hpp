@@ -54,7 +54,10 @@ __device__ void write_drive(const DriveArgs& a, uint64_t i) {
     double sA = 0.0, sB = 0.0;
     for (int k = 0; k < 4; ++k) sA = sA + OA[j * 4 + k] * hA[k];
     for (int k = 0; k < 4; ++k) sB = sB + OB[j * 4 + k] * hB[k];
-    a.drive[i * 2u + j] = (sA + sB) + a.offset;
+    const double v = (sA + sB) + a.offset;
+    if (!a.levels) a.drive[i * 2u + j] = v;
+    else if (a.dt != 0.0) ((float*)a.drive)[((uint64_t)stim * a.n_settings + s) * 2u + j] = (float)(v * a.dt);
+    else a.drive[((uint64_t)stim * a.n_settings + s) * 2u + j] = v;
   }
 }
 

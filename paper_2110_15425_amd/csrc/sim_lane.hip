@@ -26,6 +26,7 @@
 #include "lca_step.hpp"
 #include "normal64.hpp"
 #include "rng.hpp"
+#include "window.hpp"
 
 namespace cm {
 namespace {
@@ -124,84 +125,14 @@ __device__ __forceinline__ bool near_th(double q, double th, double eps) {
 }
 
 
-// Record one finished run: LDS window (or global atomics in direct mode) and
-// optional per-run dumps.
 __device__ __forceinline__ void record(const SimArgs& a, uint32_t* lds, uint32_t s_lo,
                                        const Lane& L, const double* state, int width) {
-  const uint64_t n = L.n;
-  const int c = L.choice;
-  if (a.direct) {
-    uint64_t* st = a.stats + (uint64_t)L.s * CM_NSTAT;
-    if (c >= 0) {
-      const uint32_t bin = udiv_magic((L.n - 1u) * a.n_bins, a.steps_magic);
-      atomicAdd((unsigned long long*)&a.hist[((uint64_t)L.s * 2u + c) * a.n_bins + bin], 1ull);
-      atomicAdd((unsigned long long*)&st[CM_ST_DEC0 + c], 1ull);
-      atomicAdd((unsigned long long*)&st[CM_ST_SUMN0 + c], (unsigned long long)n);
-      atomicAdd((unsigned long long*)&st[CM_ST_SUMSQ0 + c], (unsigned long long)(n * n));
-      if (c == L.target) atomicAdd((unsigned long long*)&st[CM_ST_CORRECT], 1ull);
-    } else {
-      atomicAdd((unsigned long long*)&st[CM_ST_UNDEC], 1ull);
-    }
-    if (L.flag) atomicAdd((unsigned long long*)&st[CM_ST_FLAGGED], 1ull);
-  } else {
-    const uint32_t B = a.n_bins;
-    uint32_t* rec = lds + (L.s - s_lo) * rec_words(B);
-    uint32_t* cnt = rec + 2u * B;
-    unsigned long long* sums = (unsigned long long*)(cnt + kCntWords);
-    if (c >= 0) {
-      const uint32_t bin = udiv_magic((L.n - 1u) * B, a.steps_magic);
-      atomicAdd(&rec[c * B + bin], 1u);
-      atomicAdd(&cnt[kCntDec0 + c], 1u);
-      if (c == L.target) atomicAdd(&cnt[kCntCorrect], 1u);
-      atomicAdd(&sums[c], (unsigned long long)n);
-      atomicAdd(&sums[2 + c], (unsigned long long)(n * n));
-    } else {
-      atomicAdd(&cnt[kCntUndec], 1u);
-    }
-    if (L.flag) atomicAdd(&cnt[kCntFlagged], 1u);
-  }
-  if (a.run_choice) {
-    const uint64_t idx = (uint64_t)L.s * a.trials + L.t;
-    a.run_choice[idx] = (int8_t)c;
-    a.run_step[idx] = L.n;
-    a.run_flag[idx] = L.flag ? 1 : 0;
-    if (a.run_state)
-      for (int i = 0; i < width; ++i) a.run_state[idx * width + i] = state[i];
-  }
+  count_run(a, lds, s_lo, L.s, L.t, L.n, L.choice, L.target, L.flag, state, width);
 }
 
-// Flush the LDS window into the global histogram and statistics.
+// Flush the LDS window into the global histogram, statistics and time course.
 __device__ void flush(const SimArgs& a, const uint32_t* lds, uint32_t s_lo) {
-  const uint32_t B = a.n_bins, per = 2u * B + CM_NSTAT, rw = rec_words(B);
-  for (uint32_t i = threadIdx.x; i < a.window * per; i += blockDim.x) {
-    const uint32_t w = i / per, j = i - w * per;
-    const uint64_t sg = (uint64_t)s_lo + w;
-    if (sg >= a.n_settings) continue;
-    const uint32_t* rec = lds + w * rw;
-    const uint32_t* cnt = rec + 2u * B;
-    const unsigned long long* sums = (const unsigned long long*)(cnt + kCntWords);
-    unsigned long long v;
-    unsigned long long* dst;
-    if (j < 2u * B) {
-      v = rec[j];
-      dst = (unsigned long long*)&a.hist[sg * 2u * B + j];
-    } else {
-      const uint32_t k = j - 2u * B;
-      switch (k) {
-        case CM_ST_DEC0: v = cnt[kCntDec0]; break;
-        case CM_ST_DEC1: v = cnt[kCntDec1]; break;
-        case CM_ST_UNDEC: v = cnt[kCntUndec]; break;
-        case CM_ST_CORRECT: v = cnt[kCntCorrect]; break;
-        case CM_ST_SUMN0: v = sums[0]; break;
-        case CM_ST_SUMN1: v = sums[1]; break;
-        case CM_ST_SUMSQ0: v = sums[2]; break;
-        case CM_ST_SUMSQ1: v = sums[3]; break;
-        default: v = cnt[kCntFlagged]; break;
-      }
-      dst = (unsigned long long*)&a.stats[sg * CM_NSTAT + k];
-    }
-    if (v) atomicAdd(dst, v);
-  }
+  flush_window(a, lds, s_lo);
   if (a.tc) {
     const uint32_t per_tc = a.tc_k * kTcWords;
     const unsigned long long* src =
