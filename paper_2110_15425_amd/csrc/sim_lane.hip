@@ -826,6 +826,21 @@ void sim_lane_kernel(LaneBatch batch) {
 // publishes with one release: one L2 write-back per chunk, where a fence in
 // every wavefront would write the L2 back once per wavefront.  A workgroup
 // waits for a request's preparation (acquire) only on its first chunk of it.
+//
+// A release is a fence and a wait of its own before a relaxed atomic or store:
+// the wait that ends a release -- for the L2 write-back just issued -- is left out
+// by the compiler where it knows of no load or store in flight, as here after
+// the explicit waits, and the word could then be seen on another XCD before the
+// data (stale correct-response tables in about 1 of 100 requests).
+__device__ __forceinline__ void release_agent() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __builtin_amdgcn_s_waitcnt(0);
+}
+__device__ __forceinline__ void release_system() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  __builtin_amdgcn_s_waitcnt(0);
+}
+
 template <class M>
 __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
   extern __shared__ unsigned long long lds_u64[];
@@ -939,9 +954,15 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
         base += n;
         __builtin_amdgcn_s_waitcnt(0);  // this wave's copies are stored
         __syncthreads();                // and every wave's; batch[] is free
-        if (threadIdx.x == 0) __hip_atomic_store(q.dev_tail, base, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        if (threadIdx.x == 0) {
+          release_agent();
+          __hip_atomic_store(q.dev_tail, base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
       }
-      if (threadIdx.x == 0) __hip_atomic_store(q.pull_lock, 0u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (threadIdx.x == 0) {
+        release_agent();
+        __hip_atomic_store(q.pull_lock, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       __syncthreads();
       continue;
     }
@@ -959,8 +980,10 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
       for (uint64_t j = j0 + threadIdx.x; j < j1; j += kBlock) prep_index(desc.prep, j);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(&q.prep_done[slot], 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      if (threadIdx.x == 0) {
+        release_agent();
+        __hip_atomic_fetch_add(&q.prep_done[slot], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       __syncthreads();
       continue;
     }
@@ -977,7 +1000,8 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
     __builtin_amdgcn_s_waitcnt(0);  // this wave's flushes are performed
     __syncthreads();                // and every wave's
     if (threadIdx.x == 0) {
-      const uint64_t old = __hip_atomic_fetch_add(&q.chunk_done[slot], 1ull, __ATOMIC_RELEASE,
+      release_agent();
+      const uint64_t old = __hip_atomic_fetch_add(&q.chunk_done[slot], 1ull, __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
       const bool last = old + 1ull == desc.chunk_target;
       if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every chunk's flushes
@@ -988,8 +1012,11 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
       if (desc.scored) score_sweep<kBlock / 64>(desc.score, red_d, red_k, red_c);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
-      if (threadIdx.x == 0)
-        __hip_atomic_store(&q.done[slot], desc.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      if (threadIdx.x == 0) {
+        const uint32_t ticket = desc.ticket;
+        release_system();
+        __hip_atomic_store(&q.done[slot], ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
     }
     __syncthreads();  // claim[], desc and the LDS are free for the next item
   }
