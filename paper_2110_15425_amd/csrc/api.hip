@@ -686,9 +686,9 @@ cm_status launch_rnn_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, c
   a.run_step = r->run_step;
   a.run_flag = r->run_flag;
   a.run_state = r->run_state;
-  // 16 run slots per workgroup, two workgroups per CU
-  const uint64_t want = (runs + 15) / 16;
-  const uint32_t groups = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, 2ull * h->cu_count));
+  // 16 run slots per workgroup, as many workgroups as the CUs hold
+  const uint64_t want = (runs + 15) / 16, most = (uint64_t)cm::rnn_groups_per_cu(m->precision, n) * h->cu_count;
+  const uint32_t groups = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, most));
   cm_status st = enqueue_prep(m, s, r, ws, L, stream);
   if (st != CM_OK) return st;
   hipError_t e;

@@ -20,7 +20,18 @@
 // bf16 path: each wave keeps its quarter of W (bf16, matrix-core fragment
 // order) in registers for the whole kernel; r goes through LDS as bf16 B
 // fragments.  FP64 path: W's fp64 fragments stream from L2 (512 KB does not
-// fit on chip) and r goes through LDS in fp64.
+// fit on chip) and r goes through LDS in fp64.  What bounds a step of the FP64
+// kernel at 256 units: 256 products of 64 cycles per wavefront (16,384 cycles),
+// then about 1,450 vector instructions, which one wavefront issues at one per
+// 7 cycles; two workgroups on a CU fill each other's gaps.  The stream of W must
+// keep up with the products (32 bytes per cycle and CU): loads of 16 bytes per
+// lane, contiguous over the wavefront (60 bytes per cycle from L2, against 32 with
+// 8-byte loads), one K block's at a time right behind its products, the first ones
+// of a step during the step before.  The product phase took 24.0 thousand cycles
+// with 8-byte loads issued in bursts, 18.2 now; 8,192 runs of 256 units 4.93 ms
+// before and 4.37 ms now, 512 runs 2.84 and 2.55 ms, 8,192 of 64 units 700 and
+// 616 us.  Loads 8 K blocks ahead instead of 4: 4.86 ms (registers spill); eight
+// wavefronts of two blocks each: 5.2 ms.
 //
 // Run slots are refilled as runs end: the workgroup's runs are
 // r = wg + G k, k = 0, 1, ..., handed to slots in order of slot index as
@@ -49,6 +60,40 @@ __device__ __forceinline__ bool near_th(double q, double th, double eps) {
 __device__ __forceinline__ float logistic_f(float x) {
   // 1 / (1 + e^-x) with the hardware exp2 and reciprocal
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504f * x));
+}
+
+// 1 / (1 + e^-x) in double for |x| < kLogisticMax: e^-x = 2^(k / 32) e^f with
+// |f| <= ln2 / 64, the power from a 32-entry table (LDS) and an exponent, e^f - 1
+// from a minimax polynomial (error below 2^-61 of 1), the reciprocal from
+// v_rcp_f64 (good to 2^-24) and one cubic step.  25 instructions instead of about
+// 50 for the library's exponential and division.  Larger |x|, infinities and NaN
+// take the library's.
+constexpr double kLogisticMax = 700.0;
+constexpr int kExpEntries = 32;
+__device__ const double kExpTab[kExpEntries] = {
+    0x1.0000000000000p+0, 0x1.059b0d3158574p+0, 0x1.0b5586cf9890fp+0, 0x1.11301d0125b51p+0,
+    0x1.172b83c7d517bp+0, 0x1.1d4873168b9aap+0, 0x1.2387a6e756238p+0, 0x1.29e9df51fdee1p+0,
+    0x1.306fe0a31b715p+0, 0x1.371a7373aa9cbp+0, 0x1.3dea64c123422p+0, 0x1.44e086061892dp+0,
+    0x1.4bfdad5362a27p+0, 0x1.5342b569d4f82p+0, 0x1.5ab07dd485429p+0, 0x1.6247eb03a5585p+0,
+    0x1.6a09e667f3bcdp+0, 0x1.71f75e8ec5f74p+0, 0x1.7a11473eb0187p+0, 0x1.82589994cce13p+0,
+    0x1.8ace5422aa0dbp+0, 0x1.93737b0cdc5e5p+0, 0x1.9c49182a3f090p+0, 0x1.a5503b23e255dp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b7f76f2fb5e47p+0, 0x1.c199bdd85529cp+0, 0x1.cb720dcef9069p+0,
+    0x1.d5818dcfba487p+0, 0x1.dfc97337b9b5fp+0, 0x1.ea4afa2a490dap+0, 0x1.f50765b6e4540p+0};
+
+__device__ __forceinline__ double logistic_d(double x, const double* tab) {
+  const double m = __builtin_fma(x, -0x1.71547652b82fep+5, 0x1.8p52);  // k in its low bits
+  const double kd = m - 0x1.8p52;
+  const double f = __builtin_fma(kd, -0x1.abc9e3b39803fp-61, __builtin_fma(kd, -0x1.62e42fefa39efp-6, -x));
+  const int k = (int)(uint32_t)double_bits(m);
+  const uint64_t tb = double_bits(tab[k & (kExpEntries - 1)]);
+  const double t = bits_double(tb + ((uint64_t)(uint32_t)((k >> 5) << 20) << 32));
+  double h = fma_coef(f, 0x1.6c1718e7568e2p-10, 0x1.11114f8dacd43p-7);
+  h = fma_coef(f, h, 0x1.555555554b930p-5);
+  h = fma_coef(f, h, 0x1.555555554dd39p-3);
+  h = __builtin_fma(f, h, 0.5);
+  const double d = 1.0 + __builtin_fma(t, __builtin_fma(f * f, h, f), t);
+  const double y = __builtin_amdgcn_rcp(d), e = __builtin_fma(-d, y, 1.0);
+  return __builtin_fma(y, __builtin_fma(e, e, e), y);
 }
 
 // Finished-run bookkeeping shared by both precisions (one lane per run).
@@ -267,22 +312,34 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
 // fp64 throughout.  K blocks are (b, q): units 16 b + 4 k + q, k = 0..3, which
 // is the B layout of the 16x16x4 fp64 MFMA (lane j + 16 k supplies row k).
 // ---------------------------------------------------------------------------
+// Blocks of W that a lane's load takes at once (16-byte loads where a wavefront has
+// an even number of blocks).
+__host__ __device__ constexpr int f64_load(int NB) { return NB / 4 % 2 == 0 ? 2 : 1; }
+// Workgroups of a CU, by the registers: at 128 units four of them would spill (8,192
+// runs 1.71 ms against 1.45 ms with two).
+constexpr int f64_groups(int NB) { return NB > 4 ? 2 : 4; }
+
 template <int NB>
-__global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
-  constexpr int NBW = NB / 4;
+__global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnArgs a) {
+  constexpr int NBW = NB / 4, VW = f64_load(NB), NV = NBW / VW;
   constexpr int NU = NB * 16;
-  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, j = l & 15, g = l >> 4;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, j = l & 15, g = l >> 4;
   __shared__ double rt[NB * 4][64];  // [K block (b, q)][lane]
   __shared__ double ypart[4][2][16];
   __shared__ double Rs[2][NU];
+  __shared__ double exps[kExpEntries];
   __shared__ NormLds<CM_FP64> norm;
   norm.load();
+  if (tid < kExpEntries) exps[tid] = kExpTab[tid];
   __syncthreads();
   for (int i = tid; i < 2 * NU; i += kRnnBlock) Rs[i / NU][i % NU] = a.R[i];
 
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   const uint64_t G = gridDim.x, wg = blockIdx.x;
-  const double* wf = (const double*)a.wfrag;
+  struct alignas(8 * VW) Frag {
+    double a[VW];
+  };
+  const Frag* wf = (const Frag*)a.wfrag;
 
   double x[NBW][4], gu[NBW][4];
   Slot S;
@@ -313,6 +370,15 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
     acc1 = 0.0;
   };
 
+  // W's fragments, PF K blocks ahead of their products
+  constexpr int K = NB * 4, PF = 4;
+  const Frag* wbase = wf + w * K * NV * 64 + l;
+  Frag Af[PF][NV];
+#pragma unroll
+  for (int f = 0; f < PF; ++f)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Af[f][v] = wbase[(f * NV + v) * 64];
+
   slot_begin(a, S, wg + G * (uint64_t)j);
   begin_units();
   __syncthreads();
@@ -323,32 +389,22 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
     f64x4 P[NBW];
 #pragma unroll
     for (int bw = 0; bw < NBW; ++bw) P[bw] = f64x4{0.0, 0.0, 0.0, 0.0};
-    // W's fragments come from L2: each is loaded PF K blocks ahead of its
-    // product, so that the loads' latency overlaps the products in between
-    // (one load then its product back to back waits out the whole latency).
-    constexpr int K = NB * 4, PF = 4;
-    const double* wbase = wf + (uint64_t)(w * NBW) * K * 64 + l;  // + (bw K + kb) 64
-    double Af[PF][NBW];
+    double B[PF];
 #pragma unroll
-    for (int f = 0; f < PF; ++f)
-#pragma unroll
-      for (int bw = 0; bw < NBW; ++bw) Af[f][bw] = wbase[((uint64_t)bw * K + f) * 64];
+    for (int f = 0; f < PF; ++f) B[f] = rt[f][l];
 #pragma unroll 1
     for (int kb0 = 0; kb0 < K; kb0 += PF) {
+      const int kn = kb0 + PF < K ? kb0 + PF : 0;
 #pragma unroll
       for (int f = 0; f < PF; ++f) {
-        const int kb = kb0 + f;
-        const double B = rt[kb][l];
-        double cur[NBW];
-#pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) cur[bw] = Af[f][bw];
-        // (the last PF blocks reload their own fragments: no branch in the loop)
-        const int kn = kb + PF < K ? kb + PF : kb;
-#pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) Af[f][bw] = wbase[((uint64_t)bw * K + kn) * 64];
 #pragma unroll
         for (int bw = 0; bw < NBW; ++bw)
-          P[bw] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[bw], B, P[bw], 0, 0, 0);
+          P[bw] = __builtin_amdgcn_mfma_f64_16x16x4f64(Af[f][bw / VW].a[bw % VW], B[f], P[bw], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Af[f][v] = wbase[((kn + f) * NV + v) * 64];
+        B[f] = rt[kn + f][l];  // (after the last block: block 0 of this step's r, not used)
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     __syncthreads();
@@ -359,18 +415,25 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_f64_kernel(RnnArgs a) {
     for (int bw = 0; bw < NBW; ++bw) {
       const int b = w * NBW + bw;
       double r4[4];
+      bool far = false;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const uint32_t m = (uint32_t)(8 * b + 2 * g + h);
-        const Words wd = philox(S.n - 1u, S.t, S.s, m, k0, k1);
         double xi[2];
-        normals64(wd, norm.t, xi[0], xi[1]);
+        normals64(philox(S.n - 1u, S.t, S.s, m, k0, k1), norm.t, xi[0], xi[1]);
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
           const int q = 2 * h + e;
-          x[bw][q] = (x[bw][q] + a.dt * ((P[bw][q] - x[bw][q]) + gu[bw][q])) + a.b * xi[e];
-          r4[q] = 1.0 / (1.0 + exp(-x[bw][q]));
+          x[bw][q] = __builtin_fma(a.b, xi[e], __builtin_fma(a.dt, (P[bw][q] - x[bw][q]) + gu[bw][q], x[bw][q]));
+          far |= !(fabs(x[bw][q]) < kLogisticMax);
         }
+      }
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {  // overflow, infinities, NaN
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r4[q] = 1.0 / (1.0 + exp(-x[bw][q]));
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) r4[q] = logistic_d(x[bw][q], exps);
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -437,13 +500,17 @@ __global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int bf16
       const double v = W[(uint64_t)(16u * b + i) * n + 32u * kb + 8u * k8 + item];
       ((__bf16*)out)[e] = (__bf16)(float)v;
     } else {
-      // e enumerates (b, kb4, lane).  The fp64 16x16x4 accumulator holds row
-      // 4 reg + lane/16 in register reg of a lane, so row position i of block
-      // b stands for unit 16 b + 4 (i % 4) + i / 4: each lane then holds four
-      // consecutive units (16 b + 4 g + reg), as in the bf16 layout.
-      const uint32_t lane = e & 63u;
-      const uint64_t frag = e >> 6;
-      const uint32_t kb4 = (uint32_t)(frag % (4u * NB)), b = (uint32_t)(frag / (4u * NB));
+      // e enumerates (wavefront, kb4, load, lane, block of the load): what a
+      // wavefront reads for a K block is contiguous, so its lines spread over the
+      // L2's channels.  The fp64 16x16x4 accumulator holds row 4 reg + lane/16 in
+      // register reg of a lane, so row position i of block b stands for unit
+      // 16 b + 4 (i % 4) + i / 4: each lane then holds four consecutive units
+      // (16 b + 4 g + reg), as in the bf16 layout.
+      const uint32_t VW = f64_load((int)NB), NV = NB / 4u / VW, K = 4u * NB;
+      const uint32_t lane = (uint32_t)(e / VW) & 63u;
+      const uint64_t frag = e / (64u * VW);
+      const uint32_t kb4 = (uint32_t)(frag / NV % K);
+      const uint32_t b = ((uint32_t)(frag / (NV * K)) * NV + (uint32_t)(frag % NV)) * VW + (uint32_t)(e % VW);
       const uint32_t bb = kb4 >> 2, q = kb4 & 3u, i = lane & 15u, k = lane >> 4;
       const uint32_t row = 16u * b + 4u * (i & 3u) + (i >> 2);
       ((double*)out)[e] = W[(uint64_t)row * n + 16u * bb + 4u * k + q];
@@ -467,6 +534,10 @@ hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, bool bf16, hi
   const uint32_t grid = (uint32_t)std::min<uint64_t>((total + 255) / 256, 4096);
   hipLaunchKernelGGL(rnn_prep_kernel, dim3(grid), dim3(256), 0, st, W, n, out, bf16 ? 1 : 0);
   return hipGetLastError();
+}
+
+uint32_t rnn_groups_per_cu(int precision, uint32_t n_units) {
+  return precision == CM_FP64 ? f64_groups((int)n_units / 16) : 2;
 }
 
 hipError_t launch_rnn(int precision, const RnnArgs& a, uint32_t groups, hipStream_t st) {

@@ -129,3 +129,14 @@ def test_rnn_coupled_fixed_point(prec):
     x = g["run_state"][:, 2:]
     assert np.abs(x[:, :h] - xa).max() < tol and np.abs(x[:, h:] - xb).max() < tol
     assert int(g["stats"][0, 2]) == 40  # undecided at the cap
+
+
+@pytest.mark.parametrize("n_units,gain", [(64, 3e3), (192, 3e4), (256, 1e6)])
+def test_rnn_fp64_large_states(n_units, gain):
+    """Drives that carry some states past |x| = 700, where the logistic leaves
+    its table form, in the same wavefronts as small ones."""
+    w = _case(n_units, 40, seed=11, gains=np.array([1.0, gain]), max_steps=40, n_bins=10, thresh=1e300)
+    g, o = _both(w)
+    assert_parity(w, g, o, [-1])
+    x = np.abs(g["run_state"][:, 2:])
+    assert (x > 700).any() and (x < 1).any()
