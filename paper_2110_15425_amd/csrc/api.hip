@@ -686,17 +686,15 @@ cm_status launch_rnn_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, c
   a.run_step = r->run_step;
   a.run_flag = r->run_flag;
   a.run_state = r->run_state;
-  // 16 run slots per workgroup, as many workgroups as the CUs hold
-  const uint64_t want = (runs + 15) / 16, most = (uint64_t)cm::rnn_groups_per_cu(m->precision, n) * h->cu_count;
-  const uint32_t groups = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(want, most));
+  const cm::RnnPlan plan = cm::plan_rnn(m->precision, n, runs, (uint32_t)h->cu_count);
   cm_status st = enqueue_prep(m, s, r, ws, L, stream);
   if (st != CM_OK) return st;
   hipError_t e;
-  if ((e = cm::launch_rnn_prep(m->weights, n, ws + L.wfrag, m->precision != CM_FP64, stream)) != hipSuccess)
+  if ((e = cm::launch_rnn_prep(m->weights, n, ws + L.wfrag, plan.form, stream)) != hipSuccess)
     return hip_fail(e, "weight fragments");
   ProfScope prof{h, stream, timed};
   if ((e = prof.begin()) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  if ((e = cm::launch_rnn(m->precision, a, groups, stream)) != hipSuccess) return hip_fail(e, "rate-network kernel");
+  if ((e = cm::launch_rnn(plan.form, a, plan.groups, stream)) != hipSuccess) return hip_fail(e, "rate-network kernel");
   if ((e = prof.end()) != hipSuccess) return hip_fail(e, "hipEventRecord");
   return enqueue_score(m, s, r, stream);
 }

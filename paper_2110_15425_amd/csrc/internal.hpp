@@ -271,9 +271,14 @@ uint32_t lane_groups_per_cu(int kind, int precision);
 hipError_t launch_score(const ScoreBatch& b, hipStream_t st);
 uint32_t loop_team_lanes(uint32_t J, uint64_t runs, uint32_t cus);
 hipError_t launch_loop(int precision, const LoopArgs& a, uint32_t team, uint32_t blocks, hipStream_t st);
-hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, bool bf16, hipStream_t st);
-uint32_t rnn_groups_per_cu(int precision, uint32_t n_units);
-hipError_t launch_rnn(int precision, const RnnArgs& a, uint32_t groups, hipStream_t st);
+// The kernel and the workgroups of a rate-network launch.
+struct RnnPlan {
+  int form;
+  uint32_t groups;
+};
+RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t runs, uint32_t cus);
+hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, int form, hipStream_t st);
+hipError_t launch_rnn(int form, const RnnArgs& a, uint32_t groups, hipStream_t st);
 hipError_t launch_uf_init(const UnfusedArgs& a, hipStream_t st);
 hipError_t launch_uf_step(const UnfusedArgs& a, int precision, uint32_t n, int cur, uint64_t bound,
                           hipStream_t st);

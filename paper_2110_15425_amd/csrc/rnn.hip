@@ -29,8 +29,7 @@
 // 8-byte loads), one K block's at a time right behind its products, the first ones
 // of a step during the step before.  The product phase took 24.0 thousand cycles
 // with 8-byte loads issued in bursts, 18.2 now; 8,192 runs of 256 units 4.93 ms
-// before and 4.37 ms now, 512 runs 2.84 and 2.55 ms, 8,192 of 64 units 700 and
-// 616 us.  Loads 8 K blocks ahead instead of 4: 4.86 ms (registers spill); eight
+// before and 4.37 ms now, 8,192 of 64 units 700 and 616 us.  Loads 8 K blocks ahead instead of 4: 4.86 ms (registers spill); eight
 // wavefronts of two blocks each: 5.2 ms.
 //
 // Run slots are refilled as runs end: the workgroup's runs are
@@ -38,6 +37,7 @@
 // they free up.  Every wave evaluates the slot decisions identically from
 // the same LDS partial sums, so the assignment needs no atomics.
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "normal64.hpp"
@@ -52,6 +52,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRnnBlock = 256;
+enum { kFormBf16, kFormFp64, kFormFew };  // kernels, each with its own order of W
 
 __device__ __forceinline__ bool near_th(double q, double th, double eps) {
   return fabs(q - th) < eps;
@@ -481,17 +482,289 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
   }
 }
 
+// ---------------------------------------------------------------------------
+// fp64 for launches of few runs: at most eight slots in a workgroup, in groups of
+// four, each run in its slot from the start.
+//
+// The 16x16x4 product costs 64 cycles however many of its columns are runs.  The
+// 4x4x4 one (four blocks of 4 x 4) costs 16 at the same rate, so a group of four
+// runs is the unit here: A's fragment of 16 units (row i of block b in lane
+// i + 4 b + 16 k) against the same four columns in every block.  Output lane
+// j + 4 b + 16 g holds row (b, g) of run j, so with rows in order of (wavefront, b,
+// g, block of the wavefront) a lane has NBW consecutive units of each of its slots,
+// whose pairs share their random words.  What remains at one group is the stream
+// of W (512 KB for 256 units, 60 bytes per cycle and CU: 8.5 thousand cycles of a
+// step of 11 thousand).  The readout is one more product, of the rates in the
+// lane's own registers; y needs only the rates of the step before, so wavefront 0
+// decides which runs end while the others are in their products.  When a group
+// can be freed, its runs move into holes of the first.
+//
+// 256 units, 500 runs 2.55 -> 1.05 ms, 2,048 runs 2.55 -> 1.46 ms; 192 units, 1,000
+// runs 1.58 -> 0.68 ms; 128 units 0.85 -> 0.44 ms; 64 units 0.41 -> 0.31 ms (the
+// first figures: the kernel above).
+// ---------------------------------------------------------------------------
+constexpr int few_blocks(int NB) { return NB > 12 ? 4 : 2; }             // blocks of 16 units of a wavefront
+constexpr int few_waves(int NB) { return NB / few_blocks(NB); }
+// Largest launch, in runs per CU: above it the kernel above is the faster one (256
+// units, 3,000 runs 2.45 ms here and 2.56 ms there, 6,000 to 8,192 runs 3.9 to 5.1 and
+// 4.4 ms; 192 units, 3,000 runs 1.97 and 1.59 ms; 64 units, 2,048 runs 0.46 and 0.41 ms).
+constexpr uint64_t few_runs_per_cu(int NB) { return NB > 4 ? 8 : 4; }
+
+template <int NB>
+__global__ __launch_bounds__(64 * few_waves(NB), 2) void rnn_few_kernel(RnnArgs a) {
+  constexpr int NBW = few_blocks(NB), NWV = few_waves(NB), kThreads = 64 * NWV;
+  constexpr int NP = NBW / 2;              // unit pairs of a lane and slot
+  constexpr int kC = 2, kSlots = 4 * kC;
+  constexpr int K = NB * 4, PF = 8;        // K blocks of four units; W's fragments are loaded PF ahead
+  constexpr int kRow = 16 * kC + 8 / NBW;   // padded so that a wavefront's writes spread over the banks
+  constexpr int NU = NB * 16;
+  struct alignas(16) Pair {
+    double v[2];
+  };
+  // lane j + 4 b + 16 g holds units u0 .. u0 + NBW - 1 of slot 4 c + j
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int j = l & 3, b = (l >> 2) & 3, g = l >> 4;
+  const uint32_t u0 = (uint32_t)(NBW * (16 * w + 4 * b + g));
+  __shared__ Pair rt[K / 2][kRow];         // [pair of K blocks (w, b, pair)][16 c + 4 g + j]: two units of a slot
+  __shared__ double ypart[NWV][kC][32];
+  __shared__ double Rs[NWV][NBW][64];      // readout weights as A fragments (rows 0 and 1)
+  __shared__ uint4 state[kSlots];          // steps done, t, s, active | flag << 1
+  __shared__ double2 yv[kSlots];
+  __shared__ uint4 msg[kSlots];            // step index, t, s, ended | source slot << 8
+  __shared__ int ctl[2];                   // groups of the next step, slots move
+  __shared__ double exps[kExpEntries];
+  __shared__ NormLds<CM_FP64> norm;
+  norm.load();
+  for (int i = tid; i < kExpEntries; i += kThreads) exps[i] = kExpTab[i];
+  {
+    // A fragment lane i + 4 b + 16 k: row i, unit (b, k, block)
+    const int i = j, k = g;
+#pragma unroll
+    for (int bw = 0; bw < NBW; ++bw) Rs[w][bw][l] = i < 2 ? a.R[i * NU + NBW * (16 * w + 4 * b + k) + bw] : 0.0;
+  }
+
+  const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+  const uint64_t G = gridDim.x, wg = blockIdx.x;
+  const uint64_t mine = wg < a.total_runs ? (a.total_runs - wg + G - 1) / G : 0;  // runs of this workgroup, kSlots at most
+  const uint32_t slots = mine < kSlots ? (uint32_t)mine : (uint32_t)kSlots;
+  int C = (int)((slots + 3) / 4);
+  if (tid < kSlots) {
+    Slot S;
+    slot_begin(a, S, wg + G * (uint64_t)tid);
+    state[tid] = uint4{0, S.t, S.s, S.active ? 1u : 0u};
+    yv[tid] = double2{0.0, 0.0};
+  }
+  __syncthreads();
+
+  double x[kC][NBW], gu[kC][NBW];
+#pragma unroll
+  for (int c = 0; c < kC; ++c) {
+    const uint4 st = state[4 * c + j];
+    const double gd = a.n_signals ? a.grid[(uint64_t)st.z * a.n_signals] : a.gain;
+#pragma unroll
+    for (int h = 0; h < NP; ++h) {
+      double z0, z1;
+      normals64(philox(u0 / 2 + h, st.y, st.z, kStreamDrive, k0, k1), norm.t, z0, z1);
+      gu[c][2 * h] = gd * z0;
+      gu[c][2 * h + 1] = gd * z1;
+      x[c][2 * h] = x[c][2 * h + 1] = 0.0;
+      rt[(4 * w + b) * NP + h][16 * c + 4 * g + j] = Pair{{0.5, 0.5}};
+    }
+  }
+
+  const Pair* wbase = (const Pair*)a.wfrag + (uint64_t)w * K * NP * 64 + l;
+  Pair Af[PF][NP];
+#pragma unroll
+  for (int f = 0; f < PF; ++f)
+#pragma unroll
+    for (int v = 0; v < NP; ++v) Af[f][v] = wbase[(f * NP + v) * 64];
+
+  double P[kC][NBW];
+  // p = W r of this wavefront's units for the first CC groups of slots
+  auto product = [&](auto cc) {
+    constexpr int CC = decltype(cc)::value;
+    Pair B[PF / 2][CC];
+#pragma unroll
+    for (int c = 0; c < CC; ++c)
+#pragma unroll
+      for (int bw = 0; bw < NBW; ++bw) P[c][bw] = 0.0;
+#pragma unroll
+    for (int h = 0; h < PF / 2; ++h)
+#pragma unroll
+      for (int c = 0; c < CC; ++c) B[h][c] = rt[h][16 * c + 4 * g + j];
+#pragma unroll 1
+    for (int kb0 = 0; kb0 < K; kb0 += PF) {
+      const int kn = kb0 + PF < K ? kb0 + PF : 0;
+#pragma unroll
+      for (int f = 0; f < PF; ++f) {
+#pragma unroll
+        for (int bw = 0; bw < NBW; ++bw)
+#pragma unroll
+          for (int c = 0; c < CC; ++c)
+            P[c][bw] = __builtin_amdgcn_mfma_f64_4x4x4f64(Af[f][bw / 2].v[bw % 2], B[f / 2][c].v[f % 2], P[c][bw], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int v = 0; v < NP; ++v) Af[f][v] = wbase[((kn + f) * NP + v) * 64];
+        if (f % 2)  // (after the last block: this step's r once more, not used)
+#pragma unroll
+          for (int c = 0; c < CC; ++c) B[f / 2][c] = rt[(kn + f) / 2][16 * c + 4 * g + j];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+
+  // Readout, decisions and moves of the step that the other wavefronts are computing
+  auto control = [&]() {
+    const int q = l & 7, ro = (l >> 3) & 1;
+    double acc = 0.0;
+#pragma unroll
+    for (int v = 0; v < NWV; ++v) acc += ypart[v][q >> 2][16 * ro + 4 * (l >> 4) + (q & 3)];
+    acc += __shfl_xor(acc, 16, 64);
+    acc += __shfl_xor(acc, 32, 64);
+    const double oth = __shfl_xor(acc, 8, 64);
+    const uint4 st = state[q];
+    const double2 y = yv[q];
+    Slot S;
+    S.n = st.x + 1;
+    S.t = st.y;
+    S.s = st.z;
+    S.active = st.w & 1;
+    S.flag = st.w & 2;
+    S.y0 = y.x + a.dt * (st.x ? (ro ? oth : acc) : 0.0);
+    S.y1 = y.y + a.dt * (st.x ? (ro ? acc : oth) : 0.0);
+    int choice = -1;
+    const bool done = S.active && slot_decide(a, S, choice);
+    const uint32_t mask = (uint32_t)__ballot(done) & 0xFFu;
+    uint4 m = uint4{st.x, st.y, st.z, (uint32_t)q << 8};
+    int Cn = C, moved = 0;
+    if (mask) {
+      if (done && l < kSlots) record_run(a, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
+      S.active = S.active && !done;
+      m.w |= done ? 1u : 0u;
+      const uint32_t act = (uint32_t)__ballot(S.active) & 0xFFu;
+      Cn = (__builtin_popcount(act) + 3) / 4;
+      if (Cn < C) {  // the last slots in use move into the holes of the first group
+        const uint32_t low = (1u << (4 * Cn)) - 1u, holes = low & ~act;
+        uint32_t src = (uint32_t)q, rest = act & ~low;
+        if ((holes >> q) & 1u) {
+          for (uint32_t r = __builtin_popcount(holes & ((1u << q) - 1u)); r; --r) rest &= rest - 1u;
+          if (rest) src = (uint32_t)__builtin_ctz(rest);
+        }
+        m.w = (m.w & 1u) | src << 8;
+        const int from = (int)src + (l & 56);
+        S.n = __shfl(S.n, from, 64);
+        S.t = __shfl(S.t, from, 64);
+        S.s = __shfl(S.s, from, 64);
+        S.active = __shfl((int)S.active, from, 64) && q < 4 * Cn;
+        S.flag = __shfl((int)S.flag, from, 64);
+        S.y0 = __shfl(S.y0, from, 64);
+        S.y1 = __shfl(S.y1, from, 64);
+        moved = 1;
+      }
+    }
+    if (l < kSlots) {
+      state[q] = uint4{S.n, S.t, S.s, (S.active ? 1u : 0u) | (S.flag ? 2u : 0u)};
+      yv[q] = double2{S.y0, S.y1};
+      msg[q] = m;
+      if (l == 0) {
+        ctl[0] = Cn;
+        ctl[1] = moved;
+      }
+    }
+  };
+  __syncthreads();
+
+  while (C > 0) {
+    if (w == 0) control();
+    if (C == 1)
+      product(std::integral_constant<int, 1>{});
+    else
+      product(std::integral_constant<int, 2>{});
+    __syncthreads();  // all reads of rt done, control's words visible
+
+    const int Cn = __builtin_amdgcn_readfirstlane(ctl[0]), moved = __builtin_amdgcn_readfirstlane(ctl[1]);
+#pragma unroll
+    for (int c = 0; c < kC; ++c) {
+      if (c >= C) break;
+      const uint4 m = msg[4 * c + j];
+#pragma unroll
+      for (int h = 0; h < NP; ++h) {
+        double z[2];
+        normals64(philox(m.x, m.y, m.z, u0 / 2 + h, k0, k1), norm.t, z[0], z[1]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int bw = 2 * h + e;
+          x[c][bw] = __builtin_fma(a.b, z[e], __builtin_fma(a.dt, (P[c][bw] - x[c][bw]) + gu[c][bw], x[c][bw]));
+        }
+      }
+      if (a.run_state && (m.w & 1u)) {
+        double* to = a.run_state + ((uint64_t)m.z * a.trials + m.y) * (2u + a.n_units) + 2u + u0;
+#pragma unroll
+        for (int bw = 0; bw < NBW; ++bw) to[bw] = x[c][bw];
+      }
+    }
+    if (moved) {  // through this wavefront's own rows of rt
+#pragma unroll
+      for (int part = 0; part < 2; ++part) {
+        double(*v)[NBW] = part ? gu : x;
+#pragma unroll
+        for (int c = 0; c < kC; ++c)
+          if (c < C)
+#pragma unroll
+            for (int h = 0; h < NP; ++h)
+              rt[(4 * w + b) * NP + h][16 * c + 4 * g + j] = Pair{{v[c][2 * h], v[c][2 * h + 1]}};
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < kC; ++c)
+          if (c < Cn) {
+            const uint32_t src = msg[4 * c + j].w >> 8;
+#pragma unroll
+            for (int h = 0; h < NP; ++h) {
+              const Pair q = rt[(4 * w + b) * NP + h][16 * (src >> 2) + 4 * g + (src & 3)];
+              v[c][2 * h] = q.v[0];
+              v[c][2 * h + 1] = q.v[1];
+            }
+          }
+        __syncthreads();
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < kC; ++c) {
+      if (c >= Cn) break;
+      double r[NBW];
+      bool far = false;
+#pragma unroll
+      for (int bw = 0; bw < NBW; ++bw) far |= !(fabs(x[c][bw]) < kLogisticMax);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {  // overflow, infinities, NaN
+#pragma unroll
+        for (int bw = 0; bw < NBW; ++bw) r[bw] = 1.0 / (1.0 + exp(-x[c][bw]));
+      } else {
+#pragma unroll
+        for (int bw = 0; bw < NBW; ++bw) r[bw] = logistic_d(x[c][bw], exps);
+      }
+#pragma unroll
+      for (int h = 0; h < NP; ++h) rt[(4 * w + b) * NP + h][16 * c + 4 * g + j] = Pair{{r[2 * h], r[2 * h + 1]}};
+      double y = 0.0;
+#pragma unroll
+      for (int bw = 0; bw < NBW; ++bw) y = __builtin_amdgcn_mfma_f64_4x4x4f64(Rs[w][bw][l], r[bw] - 0.5, y, 0, 0, 0);
+      if (l < 32) ypart[w][c][l] = y;
+    }
+    C = Cn;
+    __syncthreads();
+  }
+}
+
 // W (fp64 row-major n x n) -> matrix-core fragment order.
 //  bf16: fragment (b, kb) for 16x16x32 MFMAs, lane l = i + 16 k8 holds
 //        W[16b + i][32kb + 8k8 + 0..7].
 //  fp64: fragment (b, kb4 = 4 bb + q), lane l = i + 16 k holds
 //        W[16b + 4 (i % 4) + i / 4][16bb + 4k + q].
-__global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int bf16) {
+__global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int form) {
   const uint32_t NB = n / 16;
   const uint64_t total = (uint64_t)n * n;
   for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (uint64_t)gridDim.x * blockDim.x) {
-    if (bf16) {
+    if (form == kFormBf16) {
       // e enumerates (b, kb, lane, item)
       const uint32_t item = e & 7u, lane = (e >> 3) & 63u, NK = NB / 2u;
       const uint64_t frag = e >> 9;
@@ -499,6 +772,18 @@ __global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int bf16
       const uint32_t i = lane & 15u, k8 = lane >> 4;
       const double v = W[(uint64_t)(16u * b + i) * n + 32u * kb + 8u * k8 + item];
       ((__bf16*)out)[e] = (__bf16)(float)v;
+    } else if (form == kFormFew) {
+      // e enumerates (wavefront w, K block, load v, lane, item).  Lane i + 4 b + 16 k
+      // of block bw = 2 v + item holds the row of unit NBW (16 w + 4 b + i) + bw and
+      // the column of unit NBW (4 kb' + k) + kw, where the K blocks are numbered
+      // NBW kb' + kw.
+      const uint32_t NBW = few_blocks((int)NB), NP = NBW / 2u, K = 4u * NB;
+      const uint32_t lane = (uint32_t)(e >> 1) & 63u, i = lane & 3u, b = (lane >> 2) & 3u, k = lane >> 4;
+      const uint64_t frag = e >> 7;
+      const uint32_t bw = 2u * (uint32_t)(frag % NP) + (uint32_t)(e & 1u), kb = (uint32_t)(frag / NP % K);
+      const uint32_t w = (uint32_t)(frag / (NP * K));
+      const uint32_t row = NBW * (16u * w + 4u * b + i) + bw, col = NBW * (4u * (kb / NBW) + k) + kb % NBW;
+      ((double*)out)[e] = W[(uint64_t)row * n + col];
     } else {
       // e enumerates (wavefront, kb4, load, lane, block of the load): what a
       // wavefront reads for a K block is contiguous, so its lines spread over the
@@ -519,33 +804,48 @@ __global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int bf16
 }
 
 template <int NB>
-hipError_t launch_nb(int precision, const RnnArgs& a, uint32_t groups, hipStream_t st) {
-  if (precision == CM_FP64)
+hipError_t launch_nb(int form, const RnnArgs& a, uint32_t groups, hipStream_t st) {
+  if (form == kFormFew)
+    hipLaunchKernelGGL((rnn_few_kernel<NB>), dim3(groups), dim3(64 * few_waves(NB)), 0, st, a);
+  else if (form == kFormFp64)
     hipLaunchKernelGGL((rnn_f64_kernel<NB>), dim3(groups), dim3(kRnnBlock), 0, st, a);
   else
     hipLaunchKernelGGL((rnn_bf16_kernel<NB>), dim3(groups), dim3(kRnnBlock), 0, st, a);
   return hipGetLastError();
 }
 
+template <int NB>
+RnnPlan plan_nb(int precision, uint64_t runs, uint64_t cus) {
+  const uint64_t wide = std::min<uint64_t>((runs + 15) / 16, cus * (precision == CM_FP64 ? f64_groups(NB) : 2));
+  if (precision != CM_FP64) return {kFormBf16, (uint32_t)wide};
+  if (runs > few_runs_per_cu(NB) * cus) return {kFormFp64, (uint32_t)wide};
+  return {kFormFew, (uint32_t)std::min<uint64_t>((runs + 3) / 4, cus)};
+}
+
 }  // namespace
 
-hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, bool bf16, hipStream_t st) {
+hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, int form, hipStream_t st) {
   const uint64_t total = (uint64_t)n * n;
   const uint32_t grid = (uint32_t)std::min<uint64_t>((total + 255) / 256, 4096);
-  hipLaunchKernelGGL(rnn_prep_kernel, dim3(grid), dim3(256), 0, st, W, n, out, bf16 ? 1 : 0);
+  hipLaunchKernelGGL(rnn_prep_kernel, dim3(grid), dim3(256), 0, st, W, n, out, form);
   return hipGetLastError();
 }
 
-uint32_t rnn_groups_per_cu(int precision, uint32_t n_units) {
-  return precision == CM_FP64 ? f64_groups((int)n_units / 16) : 2;
+RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t runs, uint32_t cus) {
+  switch (n_units) {
+    case 64: return plan_nb<4>(precision, runs, cus);
+    case 128: return plan_nb<8>(precision, runs, cus);
+    case 192: return plan_nb<12>(precision, runs, cus);
+    default: return plan_nb<16>(precision, runs, cus);
+  }
 }
 
-hipError_t launch_rnn(int precision, const RnnArgs& a, uint32_t groups, hipStream_t st) {
+hipError_t launch_rnn(int form, const RnnArgs& a, uint32_t groups, hipStream_t st) {
   switch (a.n_units) {
-    case 64: return launch_nb<4>(precision, a, groups, st);
-    case 128: return launch_nb<8>(precision, a, groups, st);
-    case 192: return launch_nb<12>(precision, a, groups, st);
-    case 256: return launch_nb<16>(precision, a, groups, st);
+    case 64: return launch_nb<4>(form, a, groups, st);
+    case 128: return launch_nb<8>(form, a, groups, st);
+    case 192: return launch_nb<12>(form, a, groups, st);
+    case 256: return launch_nb<16>(form, a, groups, st);
     default: return hipErrorInvalidValue;
   }
 }

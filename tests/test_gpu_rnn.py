@@ -131,12 +131,28 @@ def test_rnn_coupled_fixed_point(prec):
     assert int(g["stats"][0, 2]) == 40  # undecided at the cap
 
 
-@pytest.mark.parametrize("n_units,gain", [(64, 3e3), (192, 3e4), (256, 1e6)])
-def test_rnn_fp64_large_states(n_units, gain):
+@pytest.mark.parametrize("n_units,gain,trials", [(64, 3e3, 40), (192, 3e4, 40), (256, 1e6, 40), (128, 1e4, 1100)])
+def test_rnn_fp64_large_states(n_units, gain, trials):
     """Drives that carry some states past |x| = 700, where the logistic leaves
     its table form, in the same wavefronts as small ones."""
-    w = _case(n_units, 40, seed=11, gains=np.array([1.0, gain]), max_steps=40, n_bins=10, thresh=1e300)
+    w = _case(n_units, trials, seed=11, gains=np.array([1.0, gain]), max_steps=40, n_bins=10, thresh=1e300)
     g, o = _both(w)
     assert_parity(w, g, o, [-1])
     x = np.abs(g["run_state"][:, 2:])
     assert (x > 700).any() and (x < 1).any()
+
+
+@pytest.mark.parametrize("n_units,settings,trials,max_steps", [
+    (256, 1, 1, 40), (256, 1, 5, 60), (192, 3, 2, 60), (128, 1, 4, 60),  # one group and less
+    (256, 1, 1025, 30), (192, 1, 1100, 30), (128, 7, 293, 30),  # a second group in some workgroups, in all
+    (64, 1, 1024, 60), (64, 1, 1025, 60), (128, 1, 2048, 30), (128, 1, 2049, 30),  # on both sides of
+    (192, 1, 2049, 20), (256, 1, 2048, 20), (256, 1, 2049, 20),  # the rule
+])
+def test_rnn_fp64_few_runs(n_units, settings, trials, max_steps):
+    """Launches of few runs, whose groups of four slots are freed as runs end."""
+    w = _case(n_units, trials, seed=21, max_steps=max_steps, n_bins=max_steps // 2, thresh=0.1,
+              gains=None if settings == 1 else np.linspace(0.5, 2.0, settings))
+    g, o = _both(w)
+    assert_parity(w, g, o, [-1])
+    b = cm.run(w)  # without dumps
+    assert np.array_equal(b["hist"], g["hist"]) and np.array_equal(b["stats"], g["stats"])
