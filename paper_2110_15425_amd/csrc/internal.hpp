@@ -177,7 +177,11 @@ struct QueueArgs {
 // Arguments of the rate-network kernels.
 struct RnnArgs {
   uint64_t trials, n_settings, total_runs, seed;
+  uint64_t chunk;  // consecutive runs of a workgroup
+  uint64_t steps_magic;
   uint32_t max_steps, n_bins, n_signals, n_units;
+  uint32_t window;  // settings of a workgroup's LDS window
+  bool direct;      // no window: runs are counted in global memory
   double thresh, flag_eps, b, dt, gain;
   const double* grid;
   const void* wfrag;  // W in matrix-core fragment order (bf16 or fp64)
@@ -275,6 +279,7 @@ hipError_t launch_loop(int precision, const LoopArgs& a, uint32_t team, uint32_t
 struct RnnPlan {
   int form;
   uint32_t groups;
+  bool direct;  // without a window
 };
 RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t runs, uint32_t cus);
 hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, int form, hipStream_t st);

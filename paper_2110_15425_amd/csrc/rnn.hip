@@ -32,16 +32,17 @@
 // before and 4.37 ms now, 8,192 of 64 units 700 and 616 us.  Loads 8 K blocks ahead instead of 4: 4.86 ms (registers spill); eight
 // wavefronts of two blocks each: 5.2 ms.
 //
-// Run slots are refilled as runs end: the workgroup's runs are
-// r = wg + G k, k = 0, 1, ..., handed to slots in order of slot index as
-// they free up.  Every wave evaluates the slot decisions identically from
-// the same LDS partial sums, so the assignment needs no atomics.
+// Run slots are refilled as runs end: a workgroup's runs are consecutive, handed
+// to slots in order of slot index as they free up.  Every wave evaluates the slot
+// decisions identically from the same LDS partial sums, so the assignment needs
+// no atomics.  Runs are counted in an LDS window.
 #include <algorithm>
 #include <type_traits>
 
 #include "internal.hpp"
 #include "normal64.hpp"
 #include "rng.hpp"
+#include "window.hpp"
 
 namespace cm {
 namespace {
@@ -97,9 +98,43 @@ __device__ __forceinline__ double logistic_d(double x, const double* tab) {
   return __builtin_fma(y, __builtin_fma(e, e, e), y);
 }
 
-// Finished-run bookkeeping shared by both precisions (one lane per run).
-__device__ __forceinline__ void record_run(const RnnArgs& a, uint32_t s, uint32_t t, uint32_t n,
+// A workgroup's consecutive runs and the window in LDS that counts them (counted one
+// by one in global memory, 65,536 runs of 64 units, bf16, took 1.87 ms, now 1.29 ms).
+struct Work {
+  uint32_t* lds;
+  uint64_t r0;
+  uint32_t len, s_lo;
+  __device__ __forceinline__ explicit Work(const RnnArgs& a) {
+    r0 = (uint64_t)blockIdx.x * a.chunk;
+    len = (uint32_t)min(a.chunk, a.total_runs - r0);
+    s_lo = (uint32_t)(r0 / a.trials);
+    extern __shared__ unsigned long long lds_u64[];
+    lds = (uint32_t*)lds_u64;
+    for (uint32_t i = threadIdx.x; i < a.window * rec_words(a.n_bins); i += blockDim.x) lds[i] = 0u;
+    __syncthreads();
+  }
+  __device__ __forceinline__ void flush(const RnnArgs& a) const {
+    __syncthreads();
+    if (!a.direct) flush_window(a, lds, s_lo);
+  }
+};
+
+// A finished run (one lane per run).
+__device__ __forceinline__ void record_run(const RnnArgs& a, const Work& wk, uint32_t s, uint32_t t, uint32_t n,
                                            int choice, bool flag, double y0, double y1) {
+  count_run(a, wk.lds, wk.s_lo, s, t, n, choice, -1, flag, nullptr, 0);
+  if (a.run_state) {
+    const uint64_t idx = (uint64_t)s * a.trials + t;
+    a.run_state[idx * (2u + a.n_units)] = y0;
+    a.run_state[idx * (2u + a.n_units) + 1] = y1;
+  }
+}
+
+// The same in global memory always, for the few-run kernel: its workgroups have eight
+// runs at most, and the window's code in its step cost 20 to 35 us a launch (64 units,
+// 500 runs 301 and 323 us).
+__device__ __forceinline__ void record_few(const RnnArgs& a, uint32_t s, uint32_t t, uint32_t n, int choice,
+                                           bool flag, double y0, double y1) {
   uint64_t* st = a.stats + (uint64_t)s * CM_NSTAT;
   const unsigned long long nn = n;
   if (choice >= 0) {
@@ -126,17 +161,16 @@ __device__ __forceinline__ void record_run(const RnnArgs& a, uint32_t s, uint32_
 
 // Per-slot control state, identical in every lane of a slot (and every wave).
 struct Slot {
-  uint64_t run;
   uint32_t s, t, n;
   bool active, flag;
   double y0, y1;
   float acc0, acc1;  // readout sum of R (r - 1/2) for the next y update
 };
 
-__device__ __forceinline__ void slot_begin(const RnnArgs& a, Slot& S, uint64_t run) {
-  S.run = run;
-  S.active = run < a.total_runs;
-  const uint64_t r = S.active ? run : 0;
+// Run k of the workgroup, if there is one.
+__device__ __forceinline__ void slot_begin(const RnnArgs& a, const Work& wk, Slot& S, uint32_t k) {
+  S.active = k < wk.len;
+  const uint64_t r = wk.r0 + (S.active ? k : 0u);
   S.s = (uint32_t)(r / a.trials);
   S.t = (uint32_t)(r - (uint64_t)S.s * a.trials);
   S.n = 0;
@@ -164,8 +198,14 @@ __device__ __forceinline__ bool slot_decide(const RnnArgs& a, Slot& S, int& choi
 // ---------------------------------------------------------------------------
 // bf16 projection, fp32 steps, fp64 accumulators.
 // ---------------------------------------------------------------------------
+// Workgroups of a CU, as the registers allow (65,536 runs of 128 units: two 2.58 ms,
+// four 2.25 ms; of 64 units: two 1.46 ms, four and six 1.29 ms, 20,000 runs 0.56, 0.58
+// and 0.41 ms).
+constexpr int bf16_groups(int NB) { return NB > 8 ? 2 : NB > 4 ? 4 : 6; }
+
 template <int NB>
-__global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
+__global__ __launch_bounds__(kRnnBlock, bf16_groups(NB)) void rnn_bf16_kernel(RnnArgs a) {
+  const Work wk(a);
   constexpr int NBW = NB / 4;  // output blocks per wave
   constexpr int NU = NB * 16;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, j = l & 15, g = l >> 4;
@@ -190,7 +230,6 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
 
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   const float dtf = (float)a.dt, bf = (float)a.b;
-  const uint64_t G = gridDim.x, wg = blockIdx.x;
 
   double x[NBW][4];
   float gu[NBW][4];
@@ -218,7 +257,7 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
     }
   };
 
-  slot_begin(a, S, wg + G * (uint64_t)j);
+  slot_begin(a, wk, S, (uint32_t)j);
   begin_units();
   __syncthreads();
 
@@ -290,7 +329,7 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
     const uint64_t mask = __ballot(done) & 0xFFFFull;  // one bit per slot (lanes 0..15)
     if (mask) {  // uniform across the workgroup
       if (done) {
-        if (w == 0 && g == 0) record_run(a, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
+        if (w == 0 && g == 0) record_run(a, wk, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
         if (a.run_state) {
           const uint64_t idx = (uint64_t)S.s * a.trials + S.t;
 #pragma unroll
@@ -300,13 +339,14 @@ __global__ __launch_bounds__(kRnnBlock, 2) void rnn_bf16_kernel(RnnArgs a) {
               a.run_state[idx * (2u + a.n_units) + 2u + 16u * (w * NBW + bw) + 4u * g + q] = x[bw][q];
         }
         const uint32_t rank = __builtin_popcountll(mask & ((1ull << j) - 1ull));
-        slot_begin(a, S, wg + G * (uint64_t)(knext + rank));
+        slot_begin(a, wk, S, knext + rank);
         begin_units();
       }
       knext += (uint32_t)__builtin_popcountll(mask);
       __syncthreads();  // refilled slots' rt entries visible to the next projection
     }
   }
+  wk.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -322,6 +362,7 @@ constexpr int f64_groups(int NB) { return NB > 4 ? 2 : 4; }
 
 template <int NB>
 __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnArgs a) {
+  const Work wk(a);
   constexpr int NBW = NB / 4, VW = f64_load(NB), NV = NBW / VW;
   constexpr int NU = NB * 16;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, j = l & 15, g = l >> 4;
@@ -336,7 +377,6 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
   for (int i = tid; i < 2 * NU; i += kRnnBlock) Rs[i / NU][i % NU] = a.R[i];
 
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
-  const uint64_t G = gridDim.x, wg = blockIdx.x;
   struct alignas(8 * VW) Frag {
     double a[VW];
   };
@@ -380,7 +420,7 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
 #pragma unroll
     for (int v = 0; v < NV; ++v) Af[f][v] = wbase[(f * NV + v) * 64];
 
-  slot_begin(a, S, wg + G * (uint64_t)j);
+  slot_begin(a, wk, S, (uint32_t)j);
   begin_units();
   __syncthreads();
 
@@ -463,7 +503,7 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
     const uint64_t mask = __ballot(done) & 0xFFFFull;
     if (mask) {
       if (done) {
-        if (w == 0 && g == 0) record_run(a, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
+        if (w == 0 && g == 0) record_run(a, wk, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
         if (a.run_state) {
           const uint64_t idx = (uint64_t)S.s * a.trials + S.t;
 #pragma unroll
@@ -473,13 +513,14 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
               a.run_state[idx * (2u + a.n_units) + 2u + 16u * (w * NBW + bw) + 4u * g + q] = x[bw][q];
         }
         const uint32_t rank = __builtin_popcountll(mask & ((1ull << j) - 1ull));
-        slot_begin(a, S, wg + G * (uint64_t)(knext + rank));
+        slot_begin(a, wk, S, knext + rank);
         begin_units();
       }
       knext += (uint32_t)__builtin_popcountll(mask);
       __syncthreads();
     }
   }
+  wk.flush(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -545,13 +586,11 @@ __global__ __launch_bounds__(64 * few_waves(NB), 2) void rnn_few_kernel(RnnArgs 
 
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   const uint64_t G = gridDim.x, wg = blockIdx.x;
-  const uint64_t mine = wg < a.total_runs ? (a.total_runs - wg + G - 1) / G : 0;  // runs of this workgroup, kSlots at most
-  const uint32_t slots = mine < kSlots ? (uint32_t)mine : (uint32_t)kSlots;
-  int C = (int)((slots + 3) / 4);
+  int C = (int)(((a.total_runs - wg + G - 1) / G + 3) / 4);  // runs wg, wg + G, ...: kSlots at most
   if (tid < kSlots) {
-    Slot S;
-    slot_begin(a, S, wg + G * (uint64_t)tid);
-    state[tid] = uint4{0, S.t, S.s, S.active ? 1u : 0u};
+    const uint64_t run = wg + G * (uint64_t)tid, r = run < a.total_runs ? run : 0;
+    const uint32_t s = (uint32_t)(r / a.trials);
+    state[tid] = uint4{0, (uint32_t)(r - (uint64_t)s * a.trials), s, run < a.total_runs ? 1u : 0u};
     yv[tid] = double2{0.0, 0.0};
   }
   __syncthreads();
@@ -638,7 +677,7 @@ __global__ __launch_bounds__(64 * few_waves(NB), 2) void rnn_few_kernel(RnnArgs 
     uint4 m = uint4{st.x, st.y, st.z, (uint32_t)q << 8};
     int Cn = C, moved = 0;
     if (mask) {
-      if (done && l < kSlots) record_run(a, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
+      if (done && l < kSlots) record_few(a, S.s, S.t, S.n, choice, S.flag, S.y0, S.y1);
       S.active = S.active && !done;
       m.w |= done ? 1u : 0u;
       const uint32_t act = (uint32_t)__ballot(S.active) & 0xFFu;
@@ -805,21 +844,22 @@ __global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int form
 
 template <int NB>
 hipError_t launch_nb(int form, const RnnArgs& a, uint32_t groups, hipStream_t st) {
+  const size_t lds = (size_t)a.window * rec_words(a.n_bins) * 4u;
   if (form == kFormFew)
-    hipLaunchKernelGGL((rnn_few_kernel<NB>), dim3(groups), dim3(64 * few_waves(NB)), 0, st, a);
+    hipLaunchKernelGGL((rnn_few_kernel<NB>), dim3(groups), dim3(64 * few_waves(NB)), lds, st, a);
   else if (form == kFormFp64)
-    hipLaunchKernelGGL((rnn_f64_kernel<NB>), dim3(groups), dim3(kRnnBlock), 0, st, a);
+    hipLaunchKernelGGL((rnn_f64_kernel<NB>), dim3(groups), dim3(kRnnBlock), lds, st, a);
   else
-    hipLaunchKernelGGL((rnn_bf16_kernel<NB>), dim3(groups), dim3(kRnnBlock), 0, st, a);
+    hipLaunchKernelGGL((rnn_bf16_kernel<NB>), dim3(groups), dim3(kRnnBlock), lds, st, a);
   return hipGetLastError();
 }
 
 template <int NB>
 RnnPlan plan_nb(int precision, uint64_t runs, uint64_t cus) {
-  const uint64_t wide = std::min<uint64_t>((runs + 15) / 16, cus * (precision == CM_FP64 ? f64_groups(NB) : 2));
-  if (precision != CM_FP64) return {kFormBf16, (uint32_t)wide};
-  if (runs > few_runs_per_cu(NB) * cus) return {kFormFp64, (uint32_t)wide};
-  return {kFormFew, (uint32_t)std::min<uint64_t>((runs + 3) / 4, cus)};
+  const uint64_t wide = std::min<uint64_t>((runs + 15) / 16, cus * (precision == CM_FP64 ? f64_groups(NB) : bf16_groups(NB)));
+  if (precision != CM_FP64) return {kFormBf16, (uint32_t)wide, false};
+  if (runs > few_runs_per_cu(NB) * cus) return {kFormFp64, (uint32_t)wide, false};
+  return {kFormFew, (uint32_t)std::min<uint64_t>((runs + 3) / 4, cus), true};
 }
 
 }  // namespace

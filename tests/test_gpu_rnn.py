@@ -156,3 +156,19 @@ def test_rnn_fp64_few_runs(n_units, settings, trials, max_steps):
     assert_parity(w, g, o, [-1])
     b = cm.run(w)  # without dumps
     assert np.array_equal(b["hist"], g["hist"]) and np.array_equal(b["stats"], g["stats"])
+
+
+@pytest.mark.parametrize("n_units,settings,trials,n_bins", [
+    (64, 3, 500, 1200), (256, 5, 3, 1200),  # window too large: counted in global memory
+    (64, 700, 2, 40), (128, 30, 41, 40),    # many settings in a window, few
+])
+@pytest.mark.parametrize("prec", [W.FP64, W.BF16_PROJ])
+def test_rnn_counting(n_units, settings, trials, n_bins, prec):
+    """Histograms and statistics equal the reduction of the per-run outputs."""
+    from parity import reduce_dumps
+    w = _case(n_units, trials, seed=31, max_steps=max(n_bins, 60), n_bins=n_bins, thresh=0.2,
+              gains=np.linspace(0.5, 2.0, settings), precision=prec)
+    g = cm.run(w, dumps=True)
+    h, s = reduce_dumps(w, g, [-1] * settings)
+    assert np.array_equal(h, g["hist"]) and np.array_equal(s, g["stats"])
+    assert int(g["stats"][:, :3].sum()) == settings * trials
