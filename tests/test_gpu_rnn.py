@@ -133,8 +133,8 @@ def test_rnn_coupled_fixed_point(prec):
 
 @pytest.mark.parametrize("n_units,gain,trials", [(64, 3e3, 40), (192, 3e4, 40), (256, 1e6, 40), (128, 1e4, 1100)])
 def test_rnn_fp64_large_states(n_units, gain, trials):
-    """Drives that carry some states past |x| = 700, where the logistic leaves
-    its table form, in the same wavefronts as small ones."""
+    """Drives that carry some states past |x| = 80, where the logistic leaves
+    its table form, and past 700, in the same wavefronts as small ones."""
     w = _case(n_units, trials, seed=11, gains=np.array([1.0, gain]), max_steps=40, n_bins=10, thresh=1e300)
     g, o = _both(w)
     assert_parity(w, g, o, [-1])
