@@ -541,15 +541,18 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
 // decides which runs end while the others are in their products.  When a group
 // can be freed, its runs move into holes of the first.
 //
-// 256 units, 500 runs 2.55 -> 1.05 ms, 2,048 runs 2.55 -> 1.46 ms; 192 units, 1,000
-// runs 1.58 -> 0.68 ms; 128 units 0.85 -> 0.44 ms; 64 units 0.41 -> 0.31 ms (the
-// first figures: the kernel above).
+// 256 units, 500 runs 2.55 -> 1.08 ms, 2,048 runs 2.55 -> 1.43 ms; 192 units, 1,000
+// runs 1.58 -> 0.68 ms (the first figures: the kernel above).  Up to 128 units all
+// of W stays in the registers: 128 units, 500 runs 0.85 -> 0.40 -> 0.315 ms, 64 units
+// 0.41 -> 0.30 -> 0.26 ms (the middle figures: streamed).  Of 256 units 24 of the 64 K
+// blocks would fit: 500 runs 0.95 ms, but 2,048 runs 1.47 ms, from copies between the
+// register halves.
 // ---------------------------------------------------------------------------
 constexpr int few_blocks(int NB) { return NB > 12 ? 4 : 2; }             // blocks of 16 units of a wavefront
 constexpr int few_waves(int NB) { return NB / few_blocks(NB); }
 // Largest launch, in runs per CU: above it the kernel above is the faster one (256
 // units, 3,000 runs 2.45 ms here and 2.56 ms there, 6,000 to 8,192 runs 3.9 to 5.1 and
-// 4.4 ms; 192 units, 3,000 runs 1.97 and 1.59 ms; 64 units, 2,048 runs 0.46 and 0.41 ms).
+// 4.4 ms; 192 units, 3,000 runs 1.97 and 1.59 ms; 64 units, 2,048 runs 0.41 and 0.41 ms).
 constexpr uint64_t few_runs_per_cu(int NB) { return NB > 4 ? 8 : 4; }
 
 template <int NB>
@@ -612,43 +615,60 @@ __global__ __launch_bounds__(64 * few_waves(NB), 2) void rnn_few_kernel(RnnArgs 
     }
   }
 
+  // up to 128 units all of W fits in the registers, else PF K blocks do
+  constexpr bool kAll = NB <= 8;
+  constexpr int KR = kAll ? K : PF;
   const Pair* wbase = (const Pair*)a.wfrag + (uint64_t)w * K * NP * 64 + l;
-  Pair Af[PF][NP];
+  Pair Af[KR][NP];
 #pragma unroll
-  for (int f = 0; f < PF; ++f)
+  for (int f = 0; f < KR; ++f)
 #pragma unroll
     for (int v = 0; v < NP; ++v) Af[f][v] = wbase[(f * NP + v) * 64];
 
   double P[kC][NBW];
   // p = W r of this wavefront's units for the first CC groups of slots
   auto product = [&](auto cc) {
-    constexpr int CC = decltype(cc)::value;
-    Pair B[PF / 2][CC];
+    constexpr int CC = decltype(cc)::value, PB = PF / 2;
+    Pair B[PB][CC];
 #pragma unroll
     for (int c = 0; c < CC; ++c)
 #pragma unroll
       for (int bw = 0; bw < NBW; ++bw) P[c][bw] = 0.0;
 #pragma unroll
-    for (int h = 0; h < PF / 2; ++h)
+    for (int h = 0; h < PB; ++h)
 #pragma unroll
       for (int c = 0; c < CC; ++c) B[h][c] = rt[h][16 * c + 4 * g + j];
+    auto block = [&](const Pair* A, int kb) {
+#pragma unroll
+      for (int bw = 0; bw < NBW; ++bw)
+#pragma unroll
+        for (int c = 0; c < CC; ++c)
+          P[c][bw] = __builtin_amdgcn_mfma_f64_4x4x4f64(A[bw / 2].v[bw % 2], B[kb / 2 % PB][c].v[kb % 2], P[c][bw], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (kAll) {
+#pragma unroll
+      for (int kb = 0; kb < K; ++kb) {
+        block(Af[kb], kb);
+        if (kb % 2 && kb / 2 + PB < K / 2)
+#pragma unroll
+          for (int c = 0; c < CC; ++c) B[kb / 2 % PB][c] = rt[kb / 2 + PB][16 * c + 4 * g + j];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
 #pragma unroll 1
-    for (int kb0 = 0; kb0 < K; kb0 += PF) {
-      const int kn = kb0 + PF < K ? kb0 + PF : 0;
+      for (int kb0 = 0; kb0 < K; kb0 += PF) {
+        const int kn = kb0 + PF < K ? kb0 + PF : 0;
 #pragma unroll
-      for (int f = 0; f < PF; ++f) {
+        for (int f = 0; f < PF; ++f) {
+          block(Af[f], f);
 #pragma unroll
-        for (int bw = 0; bw < NBW; ++bw)
+          for (int v = 0; v < NP; ++v) Af[f][v] = wbase[((kn + f) * NP + v) * 64];
+          if (f % 2)  // (after the last block: this step's r once more, not used)
 #pragma unroll
-          for (int c = 0; c < CC; ++c)
-            P[c][bw] = __builtin_amdgcn_mfma_f64_4x4x4f64(Af[f][bw / 2].v[bw % 2], B[f / 2][c].v[f % 2], P[c][bw], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int v = 0; v < NP; ++v) Af[f][v] = wbase[((kn + f) * NP + v) * 64];
-        if (f % 2)  // (after the last block: this step's r once more, not used)
-#pragma unroll
-          for (int c = 0; c < CC; ++c) B[f / 2][c] = rt[(kn + f) / 2][16 * c + 4 * g + j];
-        __builtin_amdgcn_sched_barrier(0);
+            for (int c = 0; c < CC; ++c) B[f / 2][c] = rt[(kn + f) / 2][16 * c + 4 * g + j];
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
   };
