@@ -281,4 +281,26 @@ __device__ __forceinline__ void normals64(const Words& w, const NormTab& tab, do
 }
 
 }  // namespace
+// 53-bit uniform in (0, 1] from a word pair: ((hi:lo) >> 11) + 1, times 2^-53.
+// Built from two exact int->double conversions (the value fits in 53 bits).
+__device__ __forceinline__ double uniform53(uint32_t lo, uint32_t hi) {
+  const uint32_t top = hi >> 11;                 // bits 52..32 of the 53-bit value
+  const uint32_t bot = (hi << 21) | (lo >> 11);  // bits 31..0
+  const double v = __dadd_rn(__dmul_rn((double)top, 4294967296.0), (double)bot);
+  return __dmul_rn(__dadd_rn(v, 1.0), 0x1p-53);
+}
+
+// The same normals by the library's functions, for results that hold the states'
+// last bits: rho = sqrt(-2 ln u_a), the angle as sincospi(2 u_b), whose argument
+// reduction is exact.
+__device__ __forceinline__ void normals64_lib(const Words& w, double& z0, double& z1) {
+  const double ua = uniform53(w.w0, w.w1);
+  const double ub = uniform53(w.w2, w.w3);
+  const double rho = sqrt(__dmul_rn(-2.0, log(ua)));
+  double s, c;
+  sincospi(__dmul_rn(2.0, ub), &s, &c);
+  z0 = __dmul_rn(rho, c);
+  z1 = __dmul_rn(rho, s);
+}
+
 }  // namespace cm

@@ -206,9 +206,14 @@ __device__ __forceinline__ void wave_sync() {
 
 // Drift-diffusion (Euler-Maruyama): x <- (x + a) + b z, bounds +-theta.
 // Step n uses element (n-1) & 1 of block (n-1) >> 1.
-template <int PREC>
+//
+// EXACT (FP64 time course): its samples are whole numbers quantised from the state
+// after every interval, so the state's last bits are part of the results.  It keeps
+// the library's logarithm, square root and sine for the normals and separate products
+// and sums in the update, which the other results do not depend on.
+template <int PREC, bool EXACT = false>
 struct DDM {
-  static constexpr int kPrec = PREC;
+  static constexpr int kNorm = EXACT ? CM_FP32_STEP : PREC;  // whose table of normals
   static constexpr bool kClips = false;
   // Wavefronts per SIMD the kernel is built for when the tuning names none:
   // the double-precision polynomials' constants would take 94 registers (98 in
@@ -231,7 +236,9 @@ struct DDM {
 
   __device__ __forceinline__ Z draw(const SimArgs& A, const Words& w, const NormTab* nt) const {
     Z z;
-    if constexpr (PREC == CM_FP64) {
+    if constexpr (PREC == CM_FP64 && EXACT) {
+      normals64_lib(w, z.a, z.b);
+    } else if constexpr (PREC == CM_FP64) {
       normals64(w, *nt, z.a, z.b);
     } else {
       normals32(w, z.a, z.b);
@@ -242,7 +249,8 @@ struct DDM {
   }
 
   __device__ __forceinline__ void move(const SimArgs& A, decltype(Z::a) z) {
-    if constexpr (PREC == CM_FP64) x = __builtin_fma(A.b, z, x + a_step);
+    if constexpr (PREC == CM_FP64 && EXACT) x = (x + a_step) + A.b * z;
+    else if constexpr (PREC == CM_FP64) x = __builtin_fma(A.b, z, x + a_step);
     else x = x + (double)z;
   }
 
@@ -398,11 +406,11 @@ struct LcaDrive32 {
   float idt0, idt1;
 };
 
-template <int PREC>
+template <int PREC, bool EXACT = false>
 struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   double x0, x1;
   RunKey rk;
-  static constexpr int kPrec = PREC;
+  static constexpr int kNorm = EXACT ? CM_FP32_STEP : PREC;
   static constexpr bool kClips = true;  // SimArgs::nonneg applies
   static constexpr int kWaves = PREC == CM_FP64 ? 5 : 7;  // see DDM
   static constexpr int kWidth = 2;
@@ -427,7 +435,8 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
 
   __device__ __forceinline__ Z draw(const Words& w, const NormTab* nt) const {
     Z z;
-    if constexpr (PREC == CM_FP64) normals64(w, *nt, z.a, z.b);
+    if constexpr (PREC == CM_FP64 && EXACT) normals64_lib(w, z.a, z.b);
+    else if constexpr (PREC == CM_FP64) normals64(w, *nt, z.a, z.b);
     else normals32(w, z.a, z.b);
     return z;
   }
@@ -436,7 +445,10 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   // (FP32 steps).
   __device__ __forceinline__ void move(const SimArgs& A, const Z& z, bool nonneg, float& xf0, float& xf1) {
     double y0, y1;
-    if constexpr (PREC == CM_FP64) {
+    if constexpr (PREC == CM_FP64 && EXACT) {
+      y0 = (x0 + (((this->in0 - A.leak * x0) - A.comp * x1) * A.dt)) + A.b * z.a;
+      y1 = (x1 + (((this->in1 - A.leak * x1) - A.comp * x0) * A.dt)) + A.b * z.b;
+    } else if constexpr (PREC == CM_FP64) {
       y0 = lca_next_f64(x0, x1, this->in0, A.leak, A.comp, A.dt, A.b, z.a);
       y1 = lca_next_f64(x1, x0, this->in1, A.leak, A.comp, A.dt, A.b, z.b);
     } else {
@@ -788,7 +800,7 @@ void sim_lane_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];  // 8-byte aligned window
   __shared__ uint32_t next;
   __shared__ uint32_t drain_cnt[BLOCK / 64];
-  __shared__ NormLds<M::kPrec> norm;
+  __shared__ NormLds<M::kNorm> norm;
   norm.load();  // visible after lane_chunk's first barrier
   uint32_t sw = 0;
   while (sw + 1 < batch.n && blockIdx.x >= batch.base[sw + 1]) ++sw;
@@ -851,7 +863,7 @@ __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
   __shared__ QueueReq batch[kBlock];
   __shared__ double red_d[kBlock / 64];
   __shared__ unsigned long long red_k[kBlock / 64], red_c[kBlock / 64];
-  __shared__ NormLds<M::kPrec> norm;
+  __shared__ NormLds<M::kNorm> norm;
   norm.load();
   constexpr uint32_t kItem = 0, kQuit = 1, kPull = 2;
   uint32_t seen_slot = ~0u;  // thread 0: the request whose preparation this workgroup last waited for
@@ -1180,7 +1192,7 @@ __global__ __launch_bounds__(kScanBlockMax) void ddm_scan_kernel(LaneBatch batch
 // rate it reaches is the measured ceiling of the step's instruction mix.
 template <class M>
 __global__ __launch_bounds__(kBlock) void ceiling_kernel(SimArgs a, uint32_t steps, double* out) {
-  __shared__ NormLds<M::kPrec> norm;
+  __shared__ NormLds<M::kNorm> norm;
   norm.load();
   __syncthreads();
   const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1208,16 +1220,19 @@ void launch_occ(const LaneBatch& b, uint32_t occ, size_t lds, hipStream_t st) {
 }
 
 template <class M>
-hipError_t launch_model(const LaneBatch& b, bool tc, uint32_t occ, uint32_t block, size_t lds,
-                        hipStream_t st) {
-  if (tc)
-    hipLaunchKernelGGL((sim_lane_kernel<M, true, 0, kBlock>), dim3(b.base[b.n]), dim3(kBlock), lds, st, b);
-  else if (block == 512)
+hipError_t launch_model(const LaneBatch& b, uint32_t occ, uint32_t block, size_t lds, hipStream_t st) {
+  if (block == 512)
     launch_occ<M, 512>(b, occ, lds, st);
   else if (block == 1024)
     launch_occ<M, 1024>(b, occ, lds, st);
   else
     launch_occ<M, kBlock>(b, occ, lds, st);
+  return hipGetLastError();
+}
+
+template <class M>
+hipError_t launch_time_course(const LaneBatch& b, size_t lds, hipStream_t st) {
+  hipLaunchKernelGGL((sim_lane_kernel<M, true, 0, kBlock>), dim3(b.base[b.n]), dim3(kBlock), lds, st, b);
   return hipGetLastError();
 }
 
@@ -1237,11 +1252,17 @@ hipError_t launch_sim_lane(int kind, int precision, uint32_t scan_block, bool tc
       hipLaunchKernelGGL((ddm_scan_kernel<CM_FP32_STEP>), dim3(b.base[b.n]), dim3(scan_block), lds_bytes, st, b);
     return hipGetLastError();
   }
+  if (tc && kind == CM_DDM)
+    return precision == CM_FP64 ? launch_time_course<DDM<CM_FP64, true>>(b, lds_bytes, st)
+                                : launch_time_course<DDM<CM_FP32_STEP>>(b, lds_bytes, st);
+  if (tc)
+    return precision == CM_FP64 ? launch_time_course<LCA<CM_FP64, true>>(b, lds_bytes, st)
+                                : launch_time_course<LCA<CM_FP32_STEP>>(b, lds_bytes, st);
   if (kind == CM_DDM)
-    return precision == CM_FP64 ? launch_model<DDM<CM_FP64>>(b, tc, occ, block, lds_bytes, st)
-                                : launch_model<DDM<CM_FP32_STEP>>(b, tc, occ, block, lds_bytes, st);
-  return precision == CM_FP64 ? launch_model<LCA<CM_FP64>>(b, tc, occ, block, lds_bytes, st)
-                              : launch_model<LCA<CM_FP32_STEP>>(b, tc, occ, block, lds_bytes, st);
+    return precision == CM_FP64 ? launch_model<DDM<CM_FP64>>(b, occ, block, lds_bytes, st)
+                                : launch_model<DDM<CM_FP32_STEP>>(b, occ, block, lds_bytes, st);
+  return precision == CM_FP64 ? launch_model<LCA<CM_FP64>>(b, occ, block, lds_bytes, st)
+                              : launch_model<LCA<CM_FP32_STEP>>(b, occ, block, lds_bytes, st);
 }
 
 hipError_t launch_queue(int kind, int precision, const QueueArgs& q, uint32_t groups, size_t lds_bytes,

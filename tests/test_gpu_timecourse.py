@@ -134,3 +134,20 @@ def test_timecourse_rejects_bad_arguments():
     ds2 = cm.DeviceSweep(h, W.rnn(trials=16, n_units=64, max_steps=10, n_bins=5))
     with pytest.raises(cm.CmError):
         ds2.launch_timecourse(1)
+
+
+def test_timecourse_fp64_pinned():
+    """The FP64 time course holds the states' last bits (its samples are quantised
+    from them), so it is pinned: sums over 200,003 runs of the conflict network and
+    500,009 of the DDM, as the kernels have computed them from the library's normals
+    and separate products and sums."""
+    import hashlib
+
+    def digest(w, every):
+        tc = cm.timecourse(w, every)[1]
+        return hashlib.sha256(np.ascontiguousarray(tc).astype("<i8").tobytes()).hexdigest()[:32]
+
+    g = np.stack([np.linspace(0.0, 5.0, 3), np.linspace(1.0, 0.5, 3)], 1)
+    assert digest(W.conflict(trials=200_003, seed=5, grid=g, max_steps=203), 7) == "c81bee5320b6187430f66af07900b8b6"
+    assert digest(W.ddm(trials=500_009, seed=6, drifts=[0.1, 0.4], max_steps=301), 10) == \
+        "62e39d9b9d2ff442d5393a0df751dd25"
