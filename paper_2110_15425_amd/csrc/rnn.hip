@@ -29,8 +29,9 @@
 // 8-byte loads), one K block's at a time right behind its products, the first ones
 // of a step during the step before.  The product phase took 24.0 thousand cycles
 // with 8-byte loads issued in bursts, 18.2 now; 8,192 runs of 256 units 4.93 ms
-// before and 4.37 ms now, 8,192 of 64 units 700 and 616 us.  Loads 8 K blocks ahead instead of 4: 4.86 ms (registers spill); eight
-// wavefronts of two blocks each: 5.2 ms.
+// before and 4.37 ms now, 8,192 of 64 units 700 and 616 us.  Loads 8 K blocks ahead
+// instead of 4: 4.86 ms (registers spill); eight wavefronts of two blocks each: 5.2
+// ms.  Few runs have a kernel of their own.
 //
 // Run slots are refilled as runs end: a workgroup's runs are consecutive, handed
 // to slots in order of slot index as they free up.  Every wave evaluates the slot
@@ -200,12 +201,11 @@ __device__ __forceinline__ bool slot_decide(const RnnArgs& a, Slot& S, int& choi
 // bf16 projection, fp32 steps, fp64 accumulators.
 // ---------------------------------------------------------------------------
 // Workgroups of a CU, as the registers allow (65,536 runs of 128 units: two 2.58 ms,
-// four 2.25 ms; of 64 units: two 1.46 ms, four and six 1.29 ms, 20,000 runs 0.56, 0.58
-// and 0.41 ms).
-constexpr int bf16_groups(int NB) { return NB > 8 ? 2 : NB > 4 ? 4 : 6; }
+// four 2.25 ms; of 64 units: two 1.46 ms, five 1.24 ms, 20,000 runs 0.56 and 0.39 ms).
+constexpr int bf16_groups(int NB) { return NB > 8 ? 2 : NB > 4 ? 4 : 5; }
 
 template <int NB>
-__global__ __launch_bounds__(kRnnBlock, bf16_groups(NB)) void rnn_bf16_kernel(RnnArgs a) {
+__global__ __launch_bounds__(kRnnBlock, NB == 8 ? 4 : 2) void rnn_bf16_kernel(RnnArgs a) {
   const Work wk(a);
   constexpr int NBW = NB / 4;  // output blocks per wave
   constexpr int NU = NB * 16;
