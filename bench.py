@@ -65,14 +65,17 @@ BATCH = 12
 # valid only for the kernel sources it was measured on, and given per
 # runs-per-lane (the number of workgroup flushes, hence the write traffic,
 # depends on it).
-TRAFFIC = {"sources_sha256": "eca0a96cb1cf47354afe1979d186ac3cf493f8d02cd39c4da3186237b32dfea4",
+TRAFFIC = {"sources_sha256": "f17483d9890f24f6e344d5df65e074f2d7e54cd5304ea8e6d6eb8fbd7f797b8c",
            "batch": 12,
            # profiles/sim_lane_lca_fp32_conflict_batched.md; key "runs_per_lane,block,tail_sweeps"
-           "bytes_per_launch": {"4,512,0": 2838118, "6,512,0": 2294170, "8,512,0": 1897882,
-                                "4,512,2": 3067904, "4,512,4": 3297690, "6,512,2": 2464154,
-                                "6,512,4": 2637210, "8,512,2": 2054144, "8,512,4": 2211430}}
+           "bytes_per_launch": {"4,256,0": 6362976, "6,256,0": 5474848, "8,256,0": 4985344, "4,256,2": 6780704,
+                                "4,256,4": 7199760, "6,256,2": 5765248, "6,256,4": 6055616, "8,256,2": 5214944,
+                                "8,256,4": 5444768, "4,512,0": 4987392, "6,512,0": 4443936, "8,512,0": 4047104,
+                                "4,512,2": 5216992, "4,512,4": 5446816, "6,512,2": 4615888, "6,512,4": 4788416,
+                                "8,512,2": 4204000, "8,512,4": 4361248}}
 KERNEL_SOURCES = ("paper_2110_15425_amd/csrc/sim_lane.hip", "paper_2110_15425_amd/csrc/rng.hpp",
-                  "paper_2110_15425_amd/csrc/lca_step.hpp", "paper_2110_15425_amd/csrc/internal.hpp",
+                  "paper_2110_15425_amd/csrc/normal64.hpp", "paper_2110_15425_amd/csrc/lca_step.hpp",
+                  "paper_2110_15425_amd/csrc/window.hpp", "paper_2110_15425_amd/csrc/internal.hpp",
                   "paper_2110_15425_amd/csrc/prep_score.hpp")
 
 
