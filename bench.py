@@ -65,7 +65,7 @@ BATCH = 12
 # valid only for the kernel sources it was measured on, and given per
 # runs-per-lane (the number of workgroup flushes, hence the write traffic,
 # depends on it).
-TRAFFIC = {"sources_sha256": "f17483d9890f24f6e344d5df65e074f2d7e54cd5304ea8e6d6eb8fbd7f797b8c",
+TRAFFIC = {"sources_sha256": "92aedc09db501b224c29307fc0f817414728982c8015ef1d95e484a77932324c",
            "batch": 12,
            # profiles/sim_lane_lca_fp32_conflict_batched.md; key "runs_per_lane,block,tail_sweeps"
            "bytes_per_launch": {"4,256,0": 6362976, "6,256,0": 5474848, "8,256,0": 4985344, "4,256,2": 6780704,

@@ -695,11 +695,11 @@ cm_status launch_rnn_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, c
   const cm::RnnPlan plan = cm::plan_rnn(m->precision, n, runs, (uint32_t)h->cu_count);
   // consecutive runs for a workgroup, counted in its LDS window where that is small
   a.steps_magic = cm::udiv_magic_for(s->max_steps);
-  a.chunk = (runs + plan.groups - 1) / plan.groups;
-  const uint64_t window = std::min<uint64_t>((a.chunk - 1) / T + 2, S);
+  a.base = runs / plan.groups;
+  a.extra = runs % plan.groups;
+  const uint64_t window = std::min<uint64_t>((a.base + (a.extra ? 1 : 0) - 1) / T + 2, S);
   a.direct = plan.direct || window * 4u * cm::rec_words(a.n_bins) > kRnnLdsBudget;
   a.window = a.direct ? 0u : (uint32_t)window;
-  const uint32_t groups = (uint32_t)((runs + a.chunk - 1) / a.chunk);
   cm_status st = enqueue_prep(m, s, r, ws, L, stream);
   if (st != CM_OK) return st;
   hipError_t e;
@@ -707,7 +707,7 @@ cm_status launch_rnn_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, c
     return hip_fail(e, "weight fragments");
   ProfScope prof{h, stream, timed};
   if ((e = prof.begin()) != hipSuccess) return hip_fail(e, "hipEventRecord");
-  if ((e = cm::launch_rnn(plan.form, a, groups, stream)) != hipSuccess) return hip_fail(e, "rate-network kernel");
+  if ((e = cm::launch_rnn(plan.form, a, plan.groups, stream)) != hipSuccess) return hip_fail(e, "rate-network kernel");
   if ((e = prof.end()) != hipSuccess) return hip_fail(e, "hipEventRecord");
   return enqueue_score(m, s, r, stream);
 }

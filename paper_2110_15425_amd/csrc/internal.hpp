@@ -177,7 +177,7 @@ struct QueueArgs {
 // Arguments of the rate-network kernels.
 struct RnnArgs {
   uint64_t trials, n_settings, total_runs, seed;
-  uint64_t chunk;  // consecutive runs of a workgroup
+  uint64_t base, extra;  // consecutive runs of a workgroup: one more in the first extra ones
   uint64_t steps_magic;
   uint32_t max_steps, n_bins, n_signals, n_units;
   uint32_t window;  // settings of a workgroup's LDS window

@@ -161,6 +161,7 @@ def test_rnn_fp64_few_runs(n_units, settings, trials, max_steps):
 @pytest.mark.parametrize("n_units,settings,trials,n_bins", [
     (64, 3, 500, 1200), (256, 5, 3, 1200),  # window too large: counted in global memory
     (64, 700, 2, 40), (128, 30, 41, 40),    # many settings in a window, few
+    (256, 1, 8300, 60), (256, 1, 8192, 60), (128, 7, 2400, 60),  # workgroups of 16 and 17 runs
 ])
 @pytest.mark.parametrize("prec", [W.FP64, W.BF16_PROJ])
 def test_rnn_counting(n_units, settings, trials, n_bins, prec):
