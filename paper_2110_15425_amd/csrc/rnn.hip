@@ -67,12 +67,14 @@ __device__ __forceinline__ float logistic_f(float x) {
 
 // 1 / (1 + e^-x) in double for |x| < kLogisticMax: E = e^-x = 2^(k / 32) e^f with
 // |f| <= ln2 / 64, the power from a 32-entry table (LDS) and an exponent, e^f - 1
-// from a minimax polynomial (error below 2^-61 of 1); the reciprocal of 1 + E in
-// floats (good to 2^-22, which is what the limit is for), then one cubic step on
-// its residual (1 - y) - E y, so that 1 + E is never rounded.  Mean error 0.31 ulp
-// (exponential and division of the library: 0.41) in 26 instructions instead of
-// about 50.  Larger |x|, infinities and NaN take the library's.
-constexpr double kLogisticMax = 80.0;
+// from a minimax polynomial (error below 2^-61 of 1); the hardware's reciprocal of
+// 1 + E (good to 2^-24), then one cubic step on its residual (1 - y) - E y, so that
+// 1 + E is never rounded.  Mean error 0.32 ulp over [-3, 3], 0.35 over [-30, 30] (exponential
+// and division of the library: 0.41 and 0.44) in 24 instructions instead of about 50.  A
+// reciprocal in floats is 1.5 % faster a sweep of 64 units, but overflows from x = -88 on,
+// and sweeps whose states pass that are 4 to 6 % slower.  Larger |x|, infinities and NaN
+// take the library's.
+constexpr double kLogisticMax = 700.0;
 constexpr int kExpEntries = 32;
 __device__ const double kExpTab[kExpEntries] = {
     0x1.0000000000000p+0, 0x1.059b0d3158574p+0, 0x1.0b5586cf9890fp+0, 0x1.11301d0125b51p+0,
@@ -96,8 +98,28 @@ __device__ __forceinline__ double logistic_d(double x, const double* tab) {
   h = fma_coef(f, h, 0x1.555555554dd39p-3);
   h = __builtin_fma(f, h, 0.5);
   const double E = __builtin_fma(t, __builtin_fma(f * f, h, f), t);
-  const double y = (double)__builtin_amdgcn_rcpf(1.0f + (float)E), e = __builtin_fma(-E, y, 1.0 - y);
+  const double y = __builtin_amdgcn_rcp(1.0 + E), e = __builtin_fma(-E, y, 1.0 - y);
   return __builtin_fma(y, __builtin_fma(e, e, e), y);
+}
+
+// Logistics of a lane's units.  The library's form is a branch of the whole wavefront's,
+// rarely taken, in which each unit keeps the form that its own state asks for: a run's
+// bits must not depend on the runs beside it.
+template <int N>
+__device__ __forceinline__ void logistics_d(const double* x, double* r, const double* tab) {
+  bool far = false;
+#pragma unroll
+  for (int i = 0; i < N; ++i) far |= !(fabs(x[i]) < kLogisticMax);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const double y = logistic_d(x[i], tab), z = 1.0 / (1.0 + exp(-x[i]));
+      r[i] = fabs(x[i]) < kLogisticMax ? y : z;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = logistic_d(x[i], tab);
+  }
 }
 
 // A workgroup's consecutive runs and the window in LDS that counts them (counted one
@@ -460,7 +482,6 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
     for (int bw = 0; bw < NBW; ++bw) {
       const int b = w * NBW + bw;
       double r4[4];
-      bool far = false;
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const uint32_t m = (uint32_t)(8 * b + 2 * g + h);
@@ -470,16 +491,9 @@ __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnA
         for (int e = 0; e < 2; ++e) {
           const int q = 2 * h + e;
           x[bw][q] = __builtin_fma(a.b, xi[e], __builtin_fma(a.dt, (P[bw][q] - x[bw][q]) + gu[bw][q], x[bw][q]));
-          far |= !(fabs(x[bw][q]) < kLogisticMax);
         }
       }
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {  // overflow, infinities, NaN
-#pragma unroll
-        for (int q = 0; q < 4; ++q) r4[q] = 1.0 / (1.0 + exp(-x[bw][q]));
-      } else {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) r4[q] = logistic_d(x[bw][q], exps);
-      }
+      logistics_d<4>(x[bw], r4, exps);
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int u = 16 * b + 4 * g + q;
@@ -795,16 +809,7 @@ __global__ __launch_bounds__(64 * few_waves(NB), 2) void rnn_few_kernel(RnnArgs 
     for (int c = 0; c < kC; ++c) {
       if (c >= Cn) break;
       double r[NBW];
-      bool far = false;
-#pragma unroll
-      for (int bw = 0; bw < NBW; ++bw) far |= !(fabs(x[c][bw]) < kLogisticMax);
-      if (__builtin_expect(__builtin_amdgcn_ballot_w64(far) != 0, 0)) {  // overflow, infinities, NaN
-#pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) r[bw] = 1.0 / (1.0 + exp(-x[c][bw]));
-      } else {
-#pragma unroll
-        for (int bw = 0; bw < NBW; ++bw) r[bw] = logistic_d(x[c][bw], exps);
-      }
+      logistics_d<NBW>(x[c], r, exps);
 #pragma unroll
       for (int h = 0; h < NP; ++h) rt[(4 * w + b) * NP + h][16 * c + 4 * g + j] = Pair{{r[2 * h], r[2 * h + 1]}};
       double y = 0.0;

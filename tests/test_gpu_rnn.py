@@ -173,3 +173,18 @@ def test_rnn_counting(n_units, settings, trials, n_bins, prec):
     h, s = reduce_dumps(w, g, [-1] * settings)
     assert np.array_equal(h, g["hist"]) and np.array_equal(s, g["stats"])
     assert int(g["stats"][:, :3].sum()) == settings * trials
+
+
+@pytest.mark.parametrize("n_units,settings", [(64, 100), (128, 100), (192, 100), (256, 100),  # launches of few runs
+                                              (64, 600), (128, 600), (192, 600), (256, 600)])
+def test_rnn_fp64_companions(n_units, settings):
+    """A run's bits do not depend on the runs beside it: the even settings' states with
+    and without odd settings whose units leave the logistic's table form."""
+    kw = dict(n_units=n_units, trials=4, seed=41, max_steps=30, n_bins=10, thresh=1e300)
+    print(f"rnn companions {n_units} units {settings} settings", flush=True)
+    tame = np.linspace(0.5, 1.5, settings)
+    wild = tame.copy()
+    wild[1::2] = 3e4
+    a, b = (cm.run(W.rnn(gains=g, **kw), dumps=True)["run_state"].reshape(settings, 4, -1) for g in (tame, wild))
+    assert np.abs(b[1::2, :, 2:]).max() > 700 and np.abs(b[::2, :, 2:]).max() < 80
+    assert np.array_equal(a[::2], b[::2])
