@@ -328,7 +328,7 @@ cm_status cm_launch_graph(cm_handle *h, uint32_t n, const cm_model *models,
                           void *hip_stream);
 cm_status cm_graph_clear(cm_handle *h);
 
-/* Time course: what cm_launch computes, plus ensemble statistics of the state
+/* Time course: the outputs of cm_launch, plus ensemble statistics of the state
  * over time -- the dynamics modellers study beside final outcomes (Distill,
  * Sec. 1 and 2.1), including the conflict energy of the two mutually
  * inhibiting response units that the Stroop model tracks (Sec. 4.4).  At
@@ -341,6 +341,13 @@ cm_status cm_graph_clear(cm_handle *h);
  * +-2^62, summed modulo 2^64 (integer sums: independent of run order and
  * launch shape).  The DDM has one unit (x1 = 0).  Kinds CM_DDM and
  * CM_CONFLICT_LCA, precisions FP64 and FP32_STEP; 1 <= every <= max_steps.
+ * In CM_FP64 the states behind these outputs are rounded differently from
+ * cm_launch's (the library's normals, no fused multiply-adds): one step's
+ * difference is a few units in the last place, which the model's own dynamics
+ * then carry on (a conflict LCA with comp > leak enlarges it 1 + dt (comp -
+ * leak) times per step), so run_state agrees to that and a run's choice and
+ * step are cm_launch's unless such a difference spans a threshold.  In
+ * CM_FP32_STEP the conflict LCA's outputs are cm_launch's bit for bit.
  * The launch rounds the tuned steps_per_sync to a multiple of the sampling
  * interval (in step pairs for the DDM) when the interval is at most 64 of
  * those units, so that the runs of a wavefront sample together. */

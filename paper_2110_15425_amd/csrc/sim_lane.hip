@@ -208,9 +208,10 @@ __device__ __forceinline__ void wave_sync() {
 // Step n uses element (n-1) & 1 of block (n-1) >> 1.
 //
 // EXACT (FP64 time course): its samples are whole numbers quantised from the state
-// after every interval, so the state's last bits are part of the results.  It keeps
-// the library's logarithm, square root and sine for the normals and separate products
-// and sums in the update, which the other results do not depend on.
+// after every interval, sums of which are compared bit for bit.  It keeps the library's
+// logarithm, square root and sine for the normals and separate products and sums in the
+// update.  Its states therefore differ from the other FP64 forms' by roundings, which the
+// dynamics carry on: an outcome can differ only where such a difference spans a threshold.
 template <int PREC, bool EXACT = false>
 struct DDM {
   static constexpr int kNorm = EXACT ? CM_FP32_STEP : PREC;  // whose table of normals

@@ -151,3 +151,48 @@ def test_timecourse_fp64_pinned():
     assert digest(W.conflict(trials=200_003, seed=5, grid=g, max_steps=203), 7) == "c81bee5320b6187430f66af07900b8b6"
     assert digest(W.ddm(trials=500_009, seed=6, drifts=[0.1, 0.4], max_steps=301), 10) == \
         "62e39d9b9d2ff442d5393a0df751dd25"
+
+
+def _both_entries(w, every):
+    h = cm.Handle(0)
+    a, b = cm.DeviceSweep(h, w, dumps=True), cm.DeviceSweep(h, w, dumps=True)
+    a.launch()
+    b.launch_timecourse(every)
+    return a.results(), b.results()
+
+
+# One step's difference between the two FP64 forms: the normals' (8.6 and 4 units of
+# 2^-53 of |z| <= 8.6, times the noise's b) and ten roundings of terms up to X.
+def _step_difference(b, X):
+    return 12.6 * 2.0 ** -53 * 8.6 * b + 10 * 2.0 ** -53 * X
+
+
+@pytest.mark.parametrize("case", ["lca_stable", "lca_unstable", "ddm"])
+def test_timecourse_outcomes_agree_with_launch(case):
+    """Long runs to a high threshold with no flag distance: every choice and step as
+    cm_launch's, states within what the dynamics make of one step's roundings."""
+    print(f"case {case}", flush=True)
+    g = np.stack([np.linspace(0.0, 5.0, 6), np.linspace(1.0, 0.5, 6)], 1)
+    if case == "ddm":  # |x| < 50, every difference carried on as it is
+        w = W.ddm(trials=3000, drifts=[0.0, 0.3], thresh=50.0, max_steps=3000, flag_eps=0.0)
+        bound = lambda n: n * _step_difference(0.1, 50.0)  # noqa: E731
+    elif case == "lca_stable":  # each step shrinks differences to 0.95; |I| <= 16, |x| <= 38
+        w = W.conflict(trials=3000, grid=g, leak=1.0, comp=0.5, thresh=1e3, max_steps=1000, flag_eps=0.0)
+        bound = lambda n: 20 * _step_difference(0.0317, 54.0) + 0 * n  # noqa: E731
+    else:  # each step enlarges differences and states 1.05 times: |x_k| <= 40 x 1.05^k
+        w = W.conflict(trials=20_000, grid=g, thresh=1e4, max_steps=1000, flag_eps=0.0)
+        bound = lambda n: 1.05 ** n * (21 * _step_difference(0.0317, 16.0) + n * 10 * 2.0 ** -53 * 40.0)  # noqa: E731
+    a, b = _both_entries(w, 50)
+    for k in ("run_choice", "run_step", "run_flag", "hist", "stats"):
+        assert np.array_equal(a[k], b[k]), k
+    d = np.abs(a["run_state"] - b["run_state"]).max(1)
+    n = a["run_step"].astype(np.float64)
+    print(f"largest state difference {d.max():.2e}, of its bound {(d / bound(n)).max():.3f}", flush=True)
+    assert n.mean() > 150 and (d <= bound(n)).all()
+
+
+def test_timecourse_fp32_outcomes_equal_launch():
+    g = np.stack([np.linspace(0.0, 5.0, 6), np.linspace(1.0, 0.5, 6)], 1)
+    a, b = _both_entries(W.conflict(trials=5000, grid=g, precision=W.FP32_STEP, thresh=1e3, max_steps=600), 30)
+    for k in ("run_choice", "run_step", "run_flag", "run_state", "hist", "stats"):
+        assert np.array_equal(a[k], b[k]), k
