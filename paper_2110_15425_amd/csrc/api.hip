@@ -1702,7 +1702,7 @@ cm_status cm_ddm_density(cm_handle* h, const cm_model* m, const cm_sweep* s, uin
   a.tol = tol;
   a.grid = s->grid;
   a.out = first_passage;
-  a.coarse = cm::coarse_lds_bytes() + 512 <= h->lds_per_block;
+  a.coarse = cm::coarse_lds_bytes() <= h->lds_per_block;
   if (cm::density_lds_bytes(n_cells) > h->lds_per_block)
     return fail(CM_E_INVALID, "n_cells %u needs more LDS than a workgroup has", n_cells);
   DeviceGuard guard(h->device);

@@ -150,6 +150,14 @@ namespace {
 constexpr int kCoarse = 128;        // most samples (rows of B)
 constexpr int kCoarseThreads = 512;
 constexpr int kCoarsePow = 16;      // steps per pass
+constexpr int kCoarseSlots = 3;     // cells of a thread in the full-grid steps
+
+// Static LDS beside the dynamic one.
+struct CoarseShared {
+  double red[3][kCoarseThreads / 64];
+  double resid;
+  double first[2][32];  // outputs of the full-grid steps
+};
 
 struct CoarsePlan {
   bool ok;
@@ -204,7 +212,9 @@ __host__ __device__ inline CoarsePlan coarse_plan(uint32_t cells, double th, dou
   p.E = (int)ceil(8.7 * bc + ac) + 1;
   const double far = (th + fabs(start)) / (3.8 * b), d = ceil(far * far);
   p.direct = d < 1.0 ? 1 : d > 31.0 ? 31 : (int)d;
-  p.ok = p.r <= kCoarse && d <= 31.0 && coarse_geo(density_geo(cells), p).prep <= kCoarseLds;
+  const DensityGeo g = density_geo(cells);
+  p.ok = p.r <= kCoarse && d <= 31.0 && 256u * g.NT <= (uint32_t)(kCoarseSlots * kCoarseThreads) &&
+         coarse_geo(g, p).prep <= kCoarseLds;
   return p;
 }
 
@@ -232,9 +242,10 @@ __device__ double cell_mass(double d, double h, double as, double b) {
 
 __global__ __launch_bounds__(kCoarseThreads) void ddm_density_coarse_kernel(DensityArgs a) {
   extern __shared__ double sh[];
-  __shared__ double red[3][kCoarseThreads / 64];
-  __shared__ double resid_s;
-  __shared__ double first[2][32];  // outputs of the full-grid steps
+  __shared__ CoarseShared shared;
+  auto& red = shared.red;
+  auto& first = shared.first;
+  double& resid_s = shared.resid;
   const DensityGeo geo = density_geo(a.cells);
   const int tid = (int)threadIdx.x, lane = tid & 63, l16 = lane & 15, l4 = lane >> 4;
   const int wave = (int)__builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
@@ -294,7 +305,7 @@ __global__ __launch_bounds__(kCoarseThreads) void ddm_density_coarse_kernel(Dens
   __syncthreads();
 
   // This thread's cells of the full-grid steps, as in the full-grid kernel.
-  constexpr int kSlots = 3;
+  constexpr int kSlots = kCoarseSlots;
   double upc[kSlots], loc[kSlots];
   int pos[kSlots], cell[kSlots];
   double sv = 0.0, pu = 0.0, pw = 0.0;
@@ -911,7 +922,7 @@ __global__ __launch_bounds__(MAXT) void ddm_density_kernel(DensityArgs a) {
 
 }  // namespace
 
-size_t coarse_lds_bytes() { return kCoarseLds * sizeof(double); }
+size_t coarse_lds_bytes() { return kCoarseLds * sizeof(double) + sizeof(CoarseShared); }
 
 // LDS: the kernel row, two zero-padded mass vectors, the partial sums and
 // the window's row sums.
@@ -937,7 +948,7 @@ hipError_t launch_ddm_density(const DensityArgs& args, hipStream_t st) {
   a.coarse = args.coarse && p.ok && a.max_steps >= kCoarseSteps;
   if (a.coarse) {
     hipLaunchKernelGGL(ddm_density_coarse_kernel, dim3((uint32_t)a.n_settings), dim3(kCoarseThreads),
-                       coarse_lds_bytes(), st, a);
+                       kCoarseLds * sizeof(double), st, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !a.n_signals) return e;
   }

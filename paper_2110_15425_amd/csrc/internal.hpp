@@ -290,6 +290,6 @@ hipError_t launch_uf_step(const UnfusedArgs& a, int precision, uint32_t n, int c
 hipError_t launch_uf_reduce(const UnfusedArgs& a, hipStream_t st);
 hipError_t launch_ddm_density(const DensityArgs& a, hipStream_t st);
 size_t density_lds_bytes(uint32_t cells);
-size_t coarse_lds_bytes();
+size_t coarse_lds_bytes();  // all of a workgroup of the coarse form
 
 }  // namespace cm
