@@ -1700,6 +1700,7 @@ cm_status cm_ddm_density(cm_handle* h, const cm_model* m, const cm_sweep* s, uin
   a.thresh = p[CM_DDM_THRESH];
   a.start = p[CM_DDM_START];
   a.tol = tol;
+  a.tol_log = tol > 0.0 ? log(4.0 / (M_PI * tol)) : INFINITY;
   a.grid = s->grid;
   a.out = first_passage;
   a.coarse = cm::coarse_lds_bytes() <= h->lds_per_block;

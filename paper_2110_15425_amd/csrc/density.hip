@@ -195,7 +195,18 @@ static_assert(kRing * kWRows <= kOffW, "the outputs fit over B");
 // must be few enough and the kernel wide enough in cells, and neither bound so
 // unlikely (drift over noise) that its probabilities fall to the samples'
 // absolute rounding.  A NaN fails every test.
-__host__ __device__ inline CoarsePlan coarse_plan(uint32_t cells, double th, double b, double as, double start) {
+//
+// Nor may the propagation end so soon that the preparation costs more than the
+// full-grid steps it replaces: the survivor mass falls like (4 / pi) e^-(lambda n), lambda =
+// pi^2 b^2 / 8 (th + 0.583 b)^2 + as^2 / 2 b^2 (the bounds as a walk in steps meets them),
+// and is below tol after tol_log / lambda steps, tol_log = log(4 / (pi tol)); the full grid
+// then goes on for half a window and has its own start.  Fitted to measured times, us: a
+// full-grid step 1.6 at 48 to 128 cells, 2.2 at 333, 6.8 at 1,000, 12 at 1,300; the
+// preparation 51 at 48 samples, 120 at 80, 254 at 128, of 333 cells 209 at 84 and 284 at 123,
+// of 1,000 302, of 1,300 386.  With tol 0.5, us, full grid and coarse: 128 cells at noise 2.4
+// 41 and 262, 333 at 2.0 107 and 219, 333 at 1.0 230 and 306, 1,000 at 1.0 672 and 353.
+__host__ __device__ inline CoarsePlan coarse_plan(uint32_t cells, double th, double b, double as, double start,
+                                                  double tol_log) {
   CoarsePlan p{};
   const double h = (2.0 * th) / (double)cells, bc = b / h, ac = fabs(as) / h;
   if (!(bc >= 4.0) || !(2.0 * th >= 8.0 * b) || !(2.0 * fabs(as) * th <= 4.0 * b * b) || !(bc < 400.0)) return p;
@@ -212,8 +223,11 @@ __host__ __device__ inline CoarsePlan coarse_plan(uint32_t cells, double th, dou
   p.E = (int)ceil(8.7 * bc + ac) + 1;
   const double far = (th + fabs(start)) / (3.8 * b), d = ceil(far * far);
   p.direct = d < 1.0 ? 1 : d > 31.0 ? 31 : (int)d;
+  const double wide = th + 0.583 * b, lambda = 1.2337 * (b * b) / (wide * wide) + 0.5 * (as * as) / (b * b);
+  const double M = (double)cells, step_us = 1.6 + (M / 440.0) * (M / 440.0);
+  const double prep_us = 20.0 + 0.015 * (p.r * p.r) + (p.mg ? 40.0 + 0.13 * M : 0.0);
   const DensityGeo g = density_geo(cells);
-  p.ok = p.r <= kCoarse && d <= 31.0 && 256u * g.NT <= (uint32_t)(kCoarseSlots * kCoarseThreads) &&
+  p.ok = tol_log >= (p.direct - 14.0 + prep_us / step_us) * lambda && p.r <= kCoarse && d <= 31.0 && 256u * g.NT <= (uint32_t)(kCoarseSlots * kCoarseThreads) &&
          coarse_geo(g, p).prep <= kCoarseLds;
   return p;
 }
@@ -252,8 +266,11 @@ __global__ __launch_bounds__(kCoarseThreads) void ddm_density_coarse_kernel(Dens
   const uint64_t st = blockIdx.x;
   const double drift = a.n_signals ? a.grid[st * a.n_signals] : a.drift;
   const double as = drift * a.dt, b = a.b, th = a.thresh, h = (2.0 * th) / (double)a.cells;
-  CoarsePlan pl = coarse_plan(a.cells, th, b, as, a.start);
-  if (!pl.ok) return;  // the full-grid kernel's setting
+  CoarsePlan pl = coarse_plan(a.cells, th, b, as, a.start, a.tol_log);
+  if (!pl.ok) {  // the full-grid kernel's setting: no probability is negative
+    if (tid == 0) a.out[st * 2u * a.max_steps] = -1.0;
+    return;
+  }
   for (int* v : {&pl.s, &pl.mg, &pl.r, &pl.E, &pl.direct}) *v = __builtin_amdgcn_readfirstlane(*v);  // scalars
   const CoarseGeo cg = coarse_geo(geo, pl);
   const int M = (int)a.cells, NB = (int)geo.NB, NT = (int)geo.NT, s = pl.s, r = pl.r, N = (int)a.max_steps;
@@ -687,7 +704,9 @@ __global__ __launch_bounds__(MAXT) void ddm_density_kernel(DensityArgs a) {
   const double as = drift * a.dt, b = a.b, th = a.thresh, h = (2.0 * th) / (double)M;
   double* out_lo = a.out + (s * 2u) * a.max_steps;  // choice 0: lower bound
   double* out_up = out_lo + a.max_steps;             // choice 1: upper bound
-  if (a.coarse && coarse_plan(a.cells, th, b, as, a.start).ok) return;  // the coarse kernel's setting
+  // the coarse kernel's setting (a uniform test: with one per lane the steps below came out
+  // 2 to 4 % slower)
+  if (a.coarse && __builtin_amdgcn_ballot_w64(out_lo[0] != -1.0) != 0) return;
 
   if (tid == 0) {
     band[0] = 0x7FFFFFFF;
@@ -942,9 +961,10 @@ hipError_t launch_ddm_density(const DensityArgs& args, hipStream_t st) {
   if (args.cells < 16u || g.W * 64u > (uint32_t)kMaxThreads || 2u * g.W * 64u < 256u * g.NT)
     return hipErrorInvalidValue;
   // Which form a setting takes depends on its drift: known here without a
-  // grid, else both kernels run and each leaves the other's settings alone.
+  // grid, else both kernels run, the coarse one marks the settings it leaves and
+  // the other takes those.
   DensityArgs a = args;
-  const CoarsePlan p = coarse_plan(a.cells, a.thresh, a.b, a.n_signals ? 0.0 : a.drift * a.dt, a.start);
+  const CoarsePlan p = coarse_plan(a.cells, a.thresh, a.b, a.n_signals ? 0.0 : a.drift * a.dt, a.start, a.tol_log);
   a.coarse = args.coarse && p.ok && a.max_steps >= kCoarseSteps;
   if (a.coarse) {
     hipLaunchKernelGGL(ddm_density_coarse_kernel, dim3((uint32_t)a.n_settings), dim3(kCoarseThreads),

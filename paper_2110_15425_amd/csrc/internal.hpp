@@ -244,8 +244,9 @@ struct DensityArgs {
   uint64_t n_settings;
   uint32_t max_steps, cells, n_signals;
   double dt, drift, b, thresh, start, tol;
+  double tol_log;   // log(4 / (pi tol)), computed once: every place that applies a rule to it has the same
   uint32_t coarse;  // to the launcher: the device has the coarse form's LDS; to the
-                    // full-grid kernel: settings that the coarse form takes are left to it
+                    // full-grid kernel: the coarse kernel has run before it
   const double* grid;
   double* out;  // [settings][2][max_steps]
 };

@@ -20,7 +20,7 @@ void need(bool ok, const char* what, uint32_t cells, double b, double as) {
 
 void check(uint32_t cells, double b, double as) {
   using namespace cm;
-  const CoarsePlan p = coarse_plan(cells, 1.0, b, as, 0.0);
+  const CoarsePlan p = coarse_plan(cells, 1.0, b, as, 0.0, INFINITY);
   if (!p.ok) return;
   ++plans;
   const DensityGeo g = density_geo(cells);
@@ -64,9 +64,28 @@ void check(uint32_t cells, double b, double as) {
   }
 }
 
+// A propagation that ends early: the steps to the tolerance, from the discrete walk's
+// leading eigenvalue, against those that the preparation is worth.
+void check_tol(uint32_t cells, double b, double as, double tol, bool want) {
+  const cm::CoarsePlan p = cm::coarse_plan(cells, 1.0, b, as, 0.0, log(4.0 / (M_PI * tol)));
+  need(p.ok == want, want ? "left to the full grid" : "not left to the full grid", cells, b, as);
+}
+
 }  // namespace
 
 int main() {
+  check_tol(128, 0.24, 0.0, 0.5, false);   // ends after some 20 steps
+  check_tol(128, 0.24, 0.0, 1e-5, true);   // 215
+  check_tol(128, 0.1, 0.0, 0.5, false);    // 100
+  check_tol(333, 0.1, 0.0, 0.5, false);    // 100
+  check_tol(333, 0.1, 0.0, 0.1, true);     // 235
+  check_tol(333, 0.2, 0.0, 0.5, false);    // 36
+  check_tol(333, 0.2, 0.0, 1e-3, true);    // 195
+  check_tol(1000, 0.1, 0.0, 0.5, true);    // 100
+  check_tol(1000, 0.1, 0.0, 0.9, false);   // 45
+  check_tol(48, 0.2, 0.0, 1e-3, true);     // 190
+  check_tol(333, 0.1, 0.019, 1e-3, true);  // 250, with the drift
+  check_tol(333, 0.1, 0.019, 0.1, false);  // 100
   for (uint32_t cells = 16; cells <= 2000; ++cells) {
     const double lo = 4.0, hi = cells / 8.0;  // step width in cells: the rule's ends
     for (int k = 0; k <= 48 && lo <= hi; ++k) {
