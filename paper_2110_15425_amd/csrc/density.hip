@@ -140,7 +140,8 @@ namespace {
 // so that they conserve mass, or a systematic relative error of 10^-16 per step
 // would grow with the steps.  Against an 80-bit propagation (14 cases of 120 to
 // 1300 cells; norm of the error over the norm of the result) 7.8e-16 on average
-// and 3.2e-15 at most, the full-grid form 8.1e-16 and 3.5e-15.
+// and 3.2e-15 at most, the full-grid form 8.1e-16 and 3.5e-15.  An entry is off by less
+// than 2^-52 of the mass that is left before its step, besides 10^-13 of itself.
 //
 // Bound by the FP64 matrix cores of one compute unit per setting and, in the
 // passes, by latency.  64 drifts x 3000 steps x 1000 cells: 0.48 ms against
@@ -658,8 +659,8 @@ __global__ __launch_bounds__(kCoarseThreads) void ddm_density_coarse_kernel(Dens
     if (!last && ++pass < kRing) continue;
     for (int x = n0 + tid; x < end; x += kCoarseThreads) {
       const double* o = O + 3 * (x - n0);  // rows of a pass follow each other by step
-      out_up[x] = o[0];
-      out_lo[x] = o[1];
+      out_up[x] = fmax(o[0], 0.0);  // the samples' sums can fall below 0 once the mass is denormal
+      out_lo[x] = fmax(o[1], 0.0);
     }
     if (last) {
       for (int x = end + tid; x < N; x += kCoarseThreads) {
