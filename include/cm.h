@@ -448,7 +448,8 @@ cm_status cm_poll(cm_handle *h, uint64_t ticket, int *done);
  *  cm_queue_create  kind CM_CONFLICT_LCA, precision CM_FP64 or
  *                   CM_FP32_STEP (else CM_E_UNSUPPORTED); slots: requests
  *                   in flight (1..4096); groups_per_cu: persistent
- *                   workgroups per compute unit (1..4; the rest of the GPU
+ *                   workgroups per compute unit (1..4, of which the device
+ *                   holds two at a time; the rest of the GPU
  *                   stays free for other streams' kernels); idle_us: the
  *                   kernel ends after this long without an item (100 us ..
  *                   10 s) and is launched again by the next submit or poll.

@@ -435,6 +435,7 @@ struct TcSpec {
 // Kernel arguments and launch shape of one lane-kernel sweep.
 // launch_runs: runs of every sweep in the same launch (sets the automatic
 // runs per lane, which trades GPU fill against the tail of each chunk).
+// queue: for the device queue's persistent kernel instead of a launch.
 
 // Threads per workgroup of a lane-kernel launch: the tuned block; the
 // time-course variant is built for 256 only.
@@ -442,10 +443,10 @@ uint32_t lane_block(const cm_tuning& t, bool timecourse) { return timecourse ? 2
 
 cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm_result* r, char* ws,
                     const Layout& L, uint32_t scan_block, uint64_t launch_runs, const TcSpec& tc,
-                    cm::SimArgs& a, uint64_t& groups, size_t& lds, uint32_t force_block = 0) {
+                    cm::SimArgs& a, uint64_t& groups, size_t& lds, bool queue = false) {
   const bool scan = scan_block != 0;
   const cm_tuning& tune = h->tune[m->kind][m->precision];
-  const uint32_t block = force_block ? force_block : lane_block(tune, tc.every != 0);
+  const uint32_t block = queue ? 256u : lane_block(tune, tc.every != 0);
   const double* p = m->params;
   const uint64_t S = s->n_settings, T = s->trials, runs = S * T;
   const uint32_t B = s->n_bins;
@@ -518,6 +519,24 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
     // one run per lane that the GPU holds at a time
     if (rpl) {
       chunk = (uint64_t)block * rpl;
+    } else if (queue) {
+      // A chunk of the queue costs its workgroup a claim, a copy of the
+      // request's descriptor and a write-back of the L2, and the queue's
+      // workgroups (two per compute unit by default) belong to every request
+      // in flight: one chunk for every second compute unit, up to the chunks
+      // of a large launch.  Measured on MI355X, us of one request alone / of
+      // each of 16 at a time, against the rule for launches below and against
+      // two runs per lane, FP64 (FP32 steps): 37 x 27 runs 56/57, 61/46, 122/62
+      // (54/53, 56/48, 102/56; from the host's 55 us on, submission bounds the
+      // second figure); 16 x 256 65/55, 105/95, 122/60 (65/54, 104/97, 102/58);
+      // 32 x 500 97/39, 118/96, 138/53 (91/47, 119/95, 109/50); 64 x 1,000
+      // 148/31, 142/105, 150/32 (111/25, 135/104, 118/26); 2,000 x 100 209/87,
+      // 215/130, 213/89 (172/69, 192/138, 175/71); 64 x 10,000 305/213, 323/226,
+      // 324/227 (240/160, 246/164, 245/165).
+      const uint64_t most = std::max<uint64_t>(2, std::min<uint64_t>(8, launch_runs / (4096ull * cus))) * block;
+      const uint64_t want = std::max<uint64_t>(1, cus / 2u);
+      chunk = std::max<uint64_t>(4, std::min<uint64_t>(most, (launch_runs + want - 1) / want));
+      a.team_lanes = block;
     } else if (launch_runs <= once) {
       // Four workgroups per compute unit up to 2^16 runs, two up to 2^17, each
       // run held by a team of lanes from the start; then one run per lane.
@@ -1460,7 +1479,7 @@ cm_status cm_queue_submit(cm_queue* q, const cm_model* m, const cm_sweep* s, con
   uint64_t groups = 0;
   size_t lds = 0;
   if ((st = plan_lane(h, m, s, r, (char*)workspace, L, 0, s->n_settings * s->trials, TcSpec{}, a, groups, lds,
-                      256)) != CM_OK)
+                      true)) != CM_OK)
     return st;
   if (lds > q->lds) return fail(CM_E_UNSUPPORTED, "request needs more LDS than the queue kernel has");
   cm::PrepBatch pb{};

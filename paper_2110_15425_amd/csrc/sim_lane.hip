@@ -854,6 +854,10 @@ __device__ __forceinline__ void release_system() {
   __builtin_amdgcn_s_waitcnt(0);
 }
 
+// Registers and LDS hold two workgroups on a compute unit (FP64 193 registers and 59 KB,
+// FP32 steps 169 and 53 KB); more of them wait for those to end.  Bounded to three in FP32
+// steps (151 registers), a queue of two or three per compute unit serves 2,000 x 100 runs in 183
+// us alone and 79 us each, unbounded in 173 and 71.
 template <class M>
 __global__ __launch_bounds__(kBlock) void queue_kernel(QueueArgs q) {
   extern __shared__ unsigned long long lds_u64[];

@@ -1,0 +1,44 @@
+"""Launch plans of the lane kernels, on the host: what the rules send a sweep to."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2110_15425_amd import workloads as W
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LIB = os.path.join(ROOT, "paper_2110_15425_amd", "libcm.so")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    if not os.path.exists(HIPCC) and shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_check")
+    subprocess.run([HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-ffp-contract=off", "-w",
+                    "-I", os.path.join(ROOT, "include"), os.path.join(HERE, "helpers", "plan_check.hip"),
+                    "-L", os.path.dirname(LIB), "-lcm", "-Wl,-rpath," + os.path.dirname(LIB), "-o", exe],
+                   check=True, capture_output=True)
+
+    def run(where, kind, prec, settings, trials, max_steps=1000, n_bins=100, every=0):
+        r = subprocess.run([exe, where] + [str(v) for v in (kind, prec, settings, trials, max_steps, n_bins, every)],
+                           capture_output=True, text=True, check=True)
+        return dict(zip(("chunk", "groups", "team", "direct", "scan"), map(int, r.stdout.split())))
+
+    return run
+
+
+@pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
+@pytest.mark.parametrize("settings,trials", [(1, 1), (37, 27), (32, 500), (64, 1000), (1, 50_000), (2000, 100),
+                                             (64, 10_000), (64, 200_000)])
+def test_queue_chunks(plan, settings, trials, prec):
+    """A request of the device queue: few chunks, since each costs a claim, a descriptor
+    copy and a write-back of the L2, and none beyond what a large launch takes."""
+    runs = settings * trials
+    p = plan("queue", W.LCA, prec, settings, trials)
+    assert p["chunk"] * p["groups"] >= runs > p["chunk"] * (p["groups"] - 1)
+    assert 4 <= p["chunk"] <= 8 * 256 and p["team"] == 256
+    assert p["groups"] <= max(128, -(-runs // 512))
