@@ -270,8 +270,8 @@ hipError_t launch_queue(int kind, int precision, const QueueArgs& q, uint32_t gr
 // LDS after the histogram window (and the time-course blocks) that the lane
 // kernel uses to pack unfinished runs while a chunk drains.
 size_t lane_stage_bytes(int kind, int precision, uint32_t block);
-// Lane-kernel workgroups of 256 threads that a compute unit holds at a time
-// (compiler's register allocation).
+// Lane-kernel workgroups of 256 threads that a compute unit holds at a time (the
+// wavefronts per SIMD that cm_launch's default kernel is built for).
 uint32_t lane_groups_per_cu(int kind, int precision);
 hipError_t launch_score(const ScoreBatch& b, hipStream_t st);
 uint32_t loop_team_lanes(uint32_t J, uint64_t runs, uint32_t cus);

@@ -220,7 +220,9 @@ struct DDM {
   // the double-precision polynomials' constants would take 94 registers (98 in
   // the LCA) and leave 5 (4).  10^7 FP64 runs 2.10 ms at 6, 2.14 at 5; the LCA
   // spills at 6: 64 x 10^4 FP64 runs 199 us at 5, 203 at 4, 220 at 6.
-  static constexpr int kWaves = PREC == CM_FP64 ? 6 : 7;
+  // EXACT: 4 (no registers spilled; at 6, with 74 of them spilled,
+  // 1,000 runs 79 us against 72, 400,000 runs 418 and 388).
+  static constexpr int kWaves = EXACT ? 4 : PREC == CM_FP64 ? 6 : 7;
   double x, a_step;
   RunKey rk;
   static constexpr int kWidth = 1;
@@ -413,7 +415,8 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
   RunKey rk;
   static constexpr int kNorm = EXACT ? CM_FP32_STEP : PREC;
   static constexpr bool kClips = true;  // SimArgs::nonneg applies
-  static constexpr int kWaves = PREC == CM_FP64 ? 5 : 7;  // see DDM
+  static constexpr int kWaves = EXACT ? 4 : PREC == CM_FP64 ? 5 : 7;  // see DDM (EXACT at 5: 9 spilled,
+                       // 10,000 runs sampled every step 3.91 ms, at 4 2.55, every 50 steps 62.5 and 60.6 us)
   static constexpr int kWidth = 2;
 
   __device__ __forceinline__ void begin(const SimArgs& A, Lane& L, uint32_t k0, uint32_t k1) {
