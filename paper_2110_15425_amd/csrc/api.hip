@@ -590,6 +590,18 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
     if (fit >= std::min<uint64_t>(chunk, block)) chunk = fit;
     else direct = true;
   }
+  // A time course too long for the window adds its samples straight to global memory, and
+  // is bound by the atomics that meet at one word: runs that start together sample a step
+  // together.  Two runs per lane spread them over more steps at a time, which wins where
+  // many runs share a setting's words; chunks of a small launch win elsewhere, and with one
+  // setting (the words of several lie in one line).  Measured on MI355X, conflict network
+  // sampled every 3rd step, ms with two runs per lane / with the chunks of a launch: 1 x
+  // 400,000 FP32 79.8 / 92.5, 1 x 100,000 25.8 / 26.1, 1 x 64,000 16.2 / 13.2, 4 x 16,000 4.33 /
+  // 6.21, 4 x 6,000 2.02 / 2.12, 4 x 4,096 1.66 / 1.48, 16 x 4,000 1.97 / 2.52, 64 x 1,000 1.04 /
+  // 1.15, 64 x 512 0.62 / 0.61, 256 x 187 0.49 / 0.37, 2,000 x 200 3.08 / 3.41.
+  if (tc.every && direct && !tune.runs_per_lane &&
+      (launch_runs > (1ull << 16) || (launch_runs > 20000u && T > 512u && S > 1u)))
+    chunk = std::max<uint64_t>(chunk, 2ull * block);
   a.chunk = chunk;
   a.direct = direct ? 1u : 0u;
   a.window = direct ? 0 : (uint32_t)std::min<uint64_t>((chunk - 1) / T + 2, S);

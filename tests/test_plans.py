@@ -42,3 +42,15 @@ def test_queue_chunks(plan, settings, trials, prec):
     assert p["chunk"] * p["groups"] >= runs > p["chunk"] * (p["groups"] - 1)
     assert 4 <= p["chunk"] <= 8 * 256 and p["team"] == 256
     assert p["groups"] <= max(128, -(-runs // 512))
+
+
+@pytest.mark.parametrize("kind,prec", [(W.DDM, W.FP64), (W.LCA, W.FP64), (W.LCA, W.FP32_STEP)])
+@pytest.mark.parametrize("settings,trials,wide", [(1, 1000, False), (1, 65_536, False), (1, 65_537, True), (1, 400_000, True),
+                                                  (4, 5000, False), (4, 5001, True), (47, 512, False), (47, 513, True),
+                                                  (2000, 32, False), (2000, 200, True)])
+def test_sampled_in_global_memory(plan, settings, trials, wide, kind, prec):
+    """A time course whose window does not fit: two runs per lane where many runs share a
+    setting's words, else the chunks of a launch."""
+    p = plan("launch", kind, prec, settings, trials, every=1)
+    assert p["direct"] == 1 and not p["scan"]
+    assert (p["chunk"] >= 512) == wide, p
