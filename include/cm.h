@@ -197,8 +197,10 @@ typedef struct {
  *                 wavefront form runs 8 wavefronts per workgroup when the
  *                 launch has at most 2^17 runs, else 4 (the block knob
  *                 does not apply to it).
- *  waves_per_simd DDM and conflict LCA, one lane per run: 0 (the compiler's
- *                 register allocation), or 4 or 8: the kernel built with its
+ *  waves_per_simd DDM and conflict LCA, one lane per run: 0 (the number the
+ *                 library measured best: at 256 threads 6 for the DDM and 5
+ *                 for the LCA in FP64, 7 in FP32 steps, fewer in larger
+ *                 workgroups), or 4 or 8: the kernel built with its
  *                 registers capped so that 4 or 8 wavefronts fit on each
  *                 SIMD -- the register use versus occupancy study of the
  *                 paper's GPU kernels (Sec. 6.3); a cap below the kernel's

@@ -648,10 +648,13 @@ struct LCA : std::conditional<PREC == CM_FP64, LcaDrive64, LcaDrive32>::type {
 // each setting's time-course block after all the settings' records, and the
 // drain stage follows them).
 //
-// OCC: 0 leaves register allocation to the compiler; 4 or 8 caps the
-// registers so that that many wavefronts fit on each SIMD (the register use
-// versus occupancy trade-off of the paper's GPU study, Sec. 6.3; a cap below
-// the kernel's natural use spills or recomputes values).
+// OCC: 0 builds for the mechanism's own number of wavefronts per SIMD (kWaves), rounded
+// down to whole workgroups; 4 or 8 caps the registers so that that many wavefronts fit
+// (the register use versus occupancy trade-off of the paper's GPU study, Sec. 6.3; a cap
+// below the kernel's natural use spills or recomputes values).  A workgroup of 512 or 1,024
+// threads puts 2 or 4 wavefronts on every SIMD, and a bound between two multiples would cost
+// registers without another workgroup: 2 x 10^6 FP64 drift-diffusion runs, 1,024 threads, two
+// / four / eight runs per lane 841 / 628 / 518 us at 6, 807 / 610 / 507 at 4.
 // One workgroup's chunk of a sweep: runs r0 .. r0 + chunk - 1 through the
 // refill queue, the drain and the window flush.  lds: the dynamic LDS (the
 // window, then the drain stage); next, drain_cnt: the workgroup's own
@@ -798,8 +801,14 @@ __device__ __forceinline__ void lane_chunk(const SimArgs& a, uint64_t r0, uint32
   if (!a.direct) flush(a, lds, s_lo);  // the last barrier follows every record
 }
 
+template <class M, int OCC, int BLOCK>
+constexpr int lane_waves() {
+  constexpr int per = BLOCK / 256;  // wavefronts per SIMD of a workgroup
+  return OCC ? OCC : M::kWaves / per * per;
+}
+
 template <class M, bool TC, int OCC, int BLOCK>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(OCC ? OCC : M::kWaves)))
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(lane_waves<M, OCC, BLOCK>())))
 void sim_lane_kernel(LaneBatch batch) {
   extern __shared__ unsigned long long lds_u64[];  // 8-byte aligned window
   __shared__ uint32_t next;
