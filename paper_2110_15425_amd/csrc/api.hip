@@ -416,9 +416,14 @@ cm_status check_launch(const cm_model* m, const cm_sweep* s, const cm_result* r,
 
 // The DDM's wavefront-per-run scan cuts a run's latency 64-fold at similar
 // work per step; it wins while the sweep is too small to fill the GPU with
-// lanes (measured on MI355X, us per sweep, scan against lanes: at 2^18 runs of
-// one setting FP64 137 / 166, FP32 steps 109 / 117; of 61 settings at 300,000 runs
-// 153 / 168 and 122 / 120).
+// lanes.  Where that ends depends on the runs' length, which the plan does not
+// know.  Measured on MI355X, us per sweep, scan / lanes: long runs (drift 0 to
+// 0.6, some 100 steps) FP64 at 150,000 runs 95 / 131, 2^18 138 / 155, 300,000
+// 154 / 181, 420,000 203 / 211, 524,288 253 / 222; FP32 steps 70 / 103, 110 /
+// 121, 123 / 130, 160 / 143, 199 / 156; short ones (drift 2, some 50 steps)
+// FP64 76 / 72, 121 / 85, 134 / 96, 176 / 114, 222 / 117; FP32 steps 65 / 57,
+// 103 / 66, 113 / 71, 147 / 78, 185 / 83.  2^18 gives up 15 % of the long ones'
+// time in FP64 above it and up to 40 % of the short ones' below it.
 bool scan_ddm(const cm_tuning& t, uint64_t runs) {
   if (t.lanes_per_run == 64) return true;
   if (t.lanes_per_run == 1) return false;

@@ -28,3 +28,40 @@ def test_ddm_scan(prec, max_steps, flag_eps):
         for k in ("run_choice", "run_step", "run_flag", "hist", "stats"):
             assert np.array_equal(got[k], want[k]), k
         np.testing.assert_allclose(got["run_state"], want["run_state"], rtol=0, atol=400 * 4 * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
+def test_ddm_scan_with_four_wavefronts(prec):
+    """Launches of more than 2^17 runs, whose workgroups have four wavefronts."""
+    h = cm.Handle(0)
+    runs = (1 << 17) + 1
+    print(f"scan {prec} 1 x {runs}", flush=True)
+    w = W.ddm(trials=runs, seed=10, max_steps=400, precision=prec)
+    ds = cm.DeviceSweep(h, w, dumps=True)
+    ds.launch()
+    got = ds.results()
+    ds.launch_unfused()
+    want = ds.results()
+    for k in ("run_choice", "run_step", "run_flag", "hist", "stats"):
+        assert np.array_equal(got[k], want[k]), k
+    np.testing.assert_allclose(got["run_state"], want["run_state"], rtol=0, atol=400 * 4 * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
+def test_form_either_side_of_its_limit(prec):
+    """At 2^18 runs a sweep takes the scan's form, one run more takes lanes, alone and in a
+    batch beside each other: bit for bit what the form gives when it is named."""
+    kw = dict(max_steps=150, n_bins=10, precision=prec)
+    small, big = W.ddm(trials=1 << 18, seed=3, **kw), W.ddm(trials=(1 << 18) + 1, seed=4, **kw)
+    keys = ("run_state", "run_choice", "run_step", "run_flag", "hist", "stats")
+    h = cm.Handle(0)
+    print(f"limit {prec}", flush=True)
+    ds = [cm.DeviceSweep(h, w, dumps=True) for w in (small, big)]
+    cm.launch_batch(h, ds)
+    for w, d, lanes in ((small, ds[0], 64), (big, ds[1], 1)):
+        named = cm.Handle(0)
+        named.set_tuning(W.DDM, prec, lanes_per_run=lanes)
+        want, other = cm.run(w, dumps=True, handle=named), cm.run(w, dumps=True, handle=h)
+        got = d.results()
+        for k in keys:
+            assert np.array_equal(got[k], want[k]) and np.array_equal(other[k], want[k]), (lanes, k)

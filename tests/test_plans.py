@@ -54,3 +54,10 @@ def test_sampled_in_global_memory(plan, settings, trials, wide, kind, prec):
     p = plan("launch", kind, prec, settings, trials, every=1)
     assert p["direct"] == 1 and not p["scan"]
     assert (p["chunk"] >= 512) == wide, p
+
+
+@pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
+@pytest.mark.parametrize("settings,trials,scan", [(1, 1, True), (1, 1 << 18, True), (1, (1 << 18) + 1, False),
+                                                  (64, 4096, True), (64, 4097, False)])
+def test_ddm_forms(plan, settings, trials, scan, prec):
+    assert plan("launch", W.DDM, prec, settings, trials)["scan"] == scan
