@@ -509,11 +509,12 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
     // 5x10^4); 8 wavefronts per workgroup keep that chunk with half the
     // serial chain.  With one setting all of them add to one line of counters,
     // and a larger chunk pays while the launch is small: factor 4 / 5, one
-    // setting of 5,000 runs FP64 15.3 / 14.5 us, of 10,000 19.7 / 18.1, FP32
-    // 18.6 / 16.5, of 20,000 25.7 / 25.6, of 50,000 40.2 / 42.5; ten settings
-    // of 1,000 runs 15.9 / 17.9 (all with the scan's rounds through LDS).
+    // setting of 5,000 runs FP64 15.1 / 13.4 us (FP32 steps 14.7 / 12.6), 10,000
+    // 18.1 / 16.8 (17.7 / 16.1), 15,000 22.7 / 20.1 (22.7 / 19.1), 20,000 24.7 /
+    // 22.5 (23.1 / 21.0), 32,768 27.6 / 29.8 (25.9 / 26.4); ten settings of 500
+    // 11.4 / 12.8 (10.2 / 11.3), of 1,000 14.5 / 15.2 (13.3 / 13.3).
     const uint32_t waves = scan_block / 64u;
-    const double factor = S == 1 && launch_runs <= (1ull << 15) ? 5.0 : 4.0;
+    const double factor = S == 1 && launch_runs <= 30000u ? 5.0 : 4.0;
     if (!rpl)
       rpl = std::max<uint64_t>(
           1, std::min<uint64_t>(64, (uint64_t)llround(factor * sqrt((double)runs / 600.0) / waves)));

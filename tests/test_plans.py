@@ -61,3 +61,12 @@ def test_sampled_in_global_memory(plan, settings, trials, wide, kind, prec):
                                                   (64, 4096, True), (64, 4097, False)])
 def test_ddm_forms(plan, settings, trials, scan, prec):
     assert plan("launch", W.DDM, prec, settings, trials)["scan"] == scan
+
+
+@pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
+@pytest.mark.parametrize("settings,trials,chunk", [(1, 1000, 8), (1, 5000, 16), (1, 10_000, 24), (1, 20_000, 32),
+                                                   (1, 30_000, 32), (1, 32_768, 32), (10, 1000, 16), (10, 2000, 24)])
+def test_scan_chunks(plan, settings, trials, chunk, prec):
+    """Runs of a scan workgroup of eight wavefronts: five to four times sqrt(runs / 600)."""
+    p = plan("launch", W.DDM, prec, settings, trials)
+    assert p["scan"] and p["chunk"] == chunk
