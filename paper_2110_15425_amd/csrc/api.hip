@@ -731,12 +731,13 @@ cm_status launch_rnn_sweep(cm_handle* h, const cm_model* m, const cm_sweep* s, c
   a.run_step = r->run_step;
   a.run_flag = r->run_flag;
   a.run_state = r->run_state;
-  const cm::RnnPlan plan = cm::plan_rnn(m->precision, n, runs, (uint32_t)h->cu_count);
-  // consecutive runs for a workgroup, counted in its LDS window where that is small
+  const cm::RnnPlan plan = cm::plan_rnn(m->precision, n, S, runs, (uint32_t)h->cu_count);
+  // a workgroup's runs are counted in its LDS window where that is small
   a.steps_magic = cm::udiv_magic_for(s->max_steps);
   a.base = runs / plan.groups;
   a.extra = runs % plan.groups;
-  const uint64_t window = std::min<uint64_t>((a.base + (a.extra ? 1 : 0) - 1) / T + 2, S);
+  a.dealt = plan.dealt;
+  const uint64_t window = a.dealt ? S : std::min<uint64_t>((a.base + (a.extra ? 1 : 0) - 1) / T + 2, S);
   a.direct = plan.direct || window * 4u * cm::rec_words(a.n_bins) > kRnnLdsBudget;
   a.window = a.direct ? 0u : (uint32_t)window;
   cm_status st = enqueue_prep(m, s, r, ws, L, stream);

@@ -177,11 +177,12 @@ struct QueueArgs {
 // Arguments of the rate-network kernels.
 struct RnnArgs {
   uint64_t trials, n_settings, total_runs, seed;
-  uint64_t base, extra;  // consecutive runs of a workgroup: one more in the first extra ones
+  uint64_t base, extra;  // runs of a workgroup: one more in the first extra ones
   uint64_t steps_magic;
   uint32_t max_steps, n_bins, n_signals, n_units;
   uint32_t window;  // settings of a workgroup's LDS window
   bool direct;      // no window: runs are counted in global memory
+  bool dealt;       // every so-many-th run for a workgroup instead of consecutive ones
   double thresh, flag_eps, b, dt, gain;
   const double* grid;
   const void* wfrag;  // W in matrix-core fragment order (bf16 or fp64)
@@ -281,8 +282,9 @@ struct RnnPlan {
   int form;
   uint32_t groups;
   bool direct;  // without a window
+  bool dealt;
 };
-RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t runs, uint32_t cus);
+RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t settings, uint64_t runs, uint32_t cus);
 hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, int form, hipStream_t st);
 hipError_t launch_rnn(int form, const RnnArgs& a, uint32_t groups, hipStream_t st);
 hipError_t launch_uf_init(const UnfusedArgs& a, hipStream_t st);

@@ -33,8 +33,8 @@
 // instead of 4: 4.86 ms (registers spill); eight wavefronts of two blocks each: 5.2
 // ms.  Few runs have a kernel of their own.
 //
-// Run slots are refilled as runs end: a workgroup's runs are consecutive, handed
-// to slots in order of slot index as they free up.  Every wave evaluates the slot
+// Run slots are refilled as runs end: a workgroup's runs are handed to slots in
+// order of slot index as they free up.  Every wave evaluates the slot
 // decisions identically from the same LDS partial sums, so the assignment needs
 // no atomics.  Runs are counted in an LDS window.
 #include <algorithm>
@@ -122,19 +122,20 @@ __device__ __forceinline__ void logistics_d(const double* x, double* r, const do
   }
 }
 
-// A workgroup's consecutive runs and the window in LDS that counts them (counted one
-// by one in global memory, 65,536 runs of 64 units, bf16, took 1.87 ms, now 1.24 ms).
-// Workgroups differ by one run at most: rounded up alike, 8,300 runs of 256 units
-// gave 483 workgroups a seventeenth run, a round of its own (622 us), where 108 of 512
-// need one (455 us).
+// A workgroup's runs -- consecutive, or dealt out to the workgroups in turn -- and the
+// window in LDS that counts them (counted one by one in global memory, 65,536 runs of 64
+// units, bf16, took 1.87 ms, now 1.24 ms).  Workgroups differ by one run at most: rounded up
+// alike, 8,300 runs of 256 units gave 483 workgroups a seventeenth run, a round of its own
+// (622 us), where 108 of 512 need one (455 us).
+template <bool DEALT>
 struct Work {
   uint32_t* lds;
   uint64_t r0;
   uint32_t len, s_lo;
   __device__ __forceinline__ explicit Work(const RnnArgs& a) {
-    r0 = blockIdx.x * a.base + min((uint64_t)blockIdx.x, a.extra);
+    r0 = DEALT ? blockIdx.x : blockIdx.x * a.base + min((uint64_t)blockIdx.x, a.extra);
     len = (uint32_t)(a.base + (blockIdx.x < a.extra));
-    s_lo = (uint32_t)(r0 / a.trials);
+    s_lo = DEALT ? 0u : (uint32_t)(r0 / a.trials);
     extern __shared__ unsigned long long lds_u64[];
     lds = (uint32_t*)lds_u64;
     for (uint32_t i = threadIdx.x; i < a.window * rec_words(a.n_bins); i += blockDim.x) lds[i] = 0u;
@@ -147,8 +148,9 @@ struct Work {
 };
 
 // A finished run (one lane per run).
-__device__ __forceinline__ void record_run(const RnnArgs& a, const Work& wk, uint32_t s, uint32_t t, uint32_t n,
-                                           int choice, bool flag, double y0, double y1) {
+template <bool DEALT>
+__device__ __forceinline__ void record_run(const RnnArgs& a, const Work<DEALT>& wk, uint32_t s, uint32_t t,
+                                           uint32_t n, int choice, bool flag, double y0, double y1) {
   count_run(a, wk.lds, wk.s_lo, s, t, n, choice, -1, flag, nullptr, 0);
   if (a.run_state) {
     const uint64_t idx = (uint64_t)s * a.trials + t;
@@ -195,9 +197,10 @@ struct Slot {
 };
 
 // Run k of the workgroup, if there is one.
-__device__ __forceinline__ void slot_begin(const RnnArgs& a, const Work& wk, Slot& S, uint32_t k) {
+template <bool DEALT>
+__device__ __forceinline__ void slot_begin(const RnnArgs& a, const Work<DEALT>& wk, Slot& S, uint32_t k) {
   S.active = k < wk.len;
-  const uint64_t r = wk.r0 + (S.active ? k : 0u);
+  const uint64_t r = wk.r0 + (S.active ? (uint64_t)k * (DEALT ? gridDim.x : 1u) : 0u);
   S.s = (uint32_t)(r / a.trials);
   S.t = (uint32_t)(r - (uint64_t)S.s * a.trials);
   S.n = 0;
@@ -229,9 +232,9 @@ __device__ __forceinline__ bool slot_decide(const RnnArgs& a, Slot& S, int& choi
 // four 2.25 ms; of 64 units: two 1.46 ms, five 1.24 ms, 20,000 runs 0.56 and 0.39 ms).
 constexpr int bf16_groups(int NB) { return NB > 8 ? 2 : NB > 4 ? 4 : 5; }
 
-template <int NB>
+template <int NB, bool DEALT>
 __global__ __launch_bounds__(kRnnBlock, NB == 8 ? 4 : 2) void rnn_bf16_kernel(RnnArgs a) {
-  const Work wk(a);
+  const Work<DEALT> wk(a);
   constexpr int NBW = NB / 4;  // output blocks per wave
   constexpr int NU = NB * 16;
   const int tid = threadIdx.x, w = tid >> 6, l = tid & 63, j = l & 15, g = l >> 4;
@@ -388,7 +391,7 @@ constexpr int f64_groups(int NB) { return NB > 4 ? 2 : 4; }
 
 template <int NB>
 __global__ __launch_bounds__(kRnnBlock, f64_groups(NB)) void rnn_f64_kernel(RnnArgs a) {
-  const Work wk(a);
+  const Work<false> wk(a);
   constexpr int NBW = NB / 4, VW = f64_load(NB), NV = NBW / VW;
   constexpr int NU = NB * 16;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63, j = l & 15, g = l >> 4;
@@ -871,6 +874,8 @@ __global__ void rnn_prep_kernel(const double* W, uint32_t n, void* out, int form
   }
 }
 
+constexpr bool deals(int NB) { return NB > 8; }  // see plan_nb
+
 template <int NB>
 hipError_t launch_nb(int form, const RnnArgs& a, uint32_t groups, hipStream_t st) {
   const size_t lds = (size_t)a.window * rec_words(a.n_bins) * 4u;
@@ -878,17 +883,30 @@ hipError_t launch_nb(int form, const RnnArgs& a, uint32_t groups, hipStream_t st
     hipLaunchKernelGGL((rnn_few_kernel<NB>), dim3(groups), dim3(64 * few_waves(NB)), lds, st, a);
   else if (form == kFormFp64)
     hipLaunchKernelGGL((rnn_f64_kernel<NB>), dim3(groups), dim3(kRnnBlock), lds, st, a);
+  else if (deals(NB) && a.dealt)
+    hipLaunchKernelGGL((rnn_bf16_kernel<NB, deals(NB)>), dim3(groups), dim3(kRnnBlock), lds, st, a);
   else
-    hipLaunchKernelGGL((rnn_bf16_kernel<NB>), dim3(groups), dim3(kRnnBlock), lds, st, a);
+    hipLaunchKernelGGL((rnn_bf16_kernel<NB, false>), dim3(groups), dim3(kRnnBlock), lds, st, a);
   return hipGetLastError();
 }
 
+// Consecutive runs fill few windows, but belong to few settings: where settings' runs
+// differ in length so do the workgroups, and at two on a CU, all resident from the start,
+// nothing evens that out.  So bf16 networks of 192 and 256 units deal runs out in turn from
+// three settings on (with one or two, a CU's two workgroups hold both alike), where slots are
+// filled four times and more (20,000 runs of 192 units, 2.4 times, 16 gains from 0.5 to 1.5:
+// consecutive 1.23 ms, dealt 1.27, from 0.02 to 30 1.27 and 1.24): 65,536 runs of
+// 256 units with 16 gains from 0.02 to 30 consecutive 5.02 ms, dealt 4.65, 100 gains 5.03 and
+// 4.68, gains from 0.5 to 1.5 5.02 and 5.01, two gains 3.95 and 4.48; 192 units, 16 gains
+// falling from 30 to 0.02 3.53 and 3.36.  Smaller networks have four or five workgroups on a
+// CU (128 units, 16 gains 2.06 and 2.26 ms), and in FP64 it goes either way (256 units 13.6 and
+// 13.6, two gains 11.3 and 12.5, 100 falling gains 13.4 and 12.8).
 template <int NB>
-RnnPlan plan_nb(int precision, uint64_t runs, uint64_t cus) {
+RnnPlan plan_nb(int precision, uint64_t settings, uint64_t runs, uint64_t cus) {
   const uint64_t wide = std::min<uint64_t>((runs + 15) / 16, cus * (precision == CM_FP64 ? f64_groups(NB) : bf16_groups(NB)));
-  if (precision != CM_FP64) return {kFormBf16, (uint32_t)wide, false};
-  if (runs > few_runs_per_cu(NB) * cus) return {kFormFp64, (uint32_t)wide, false};
-  return {kFormFew, (uint32_t)std::min<uint64_t>((runs + 3) / 4, cus), true};
+  if (precision != CM_FP64) return {kFormBf16, (uint32_t)wide, false, deals(NB) && settings > 2 && runs >= 4u * 16u * wide};
+  if (runs > few_runs_per_cu(NB) * cus) return {kFormFp64, (uint32_t)wide, false, false};
+  return {kFormFew, (uint32_t)std::min<uint64_t>((runs + 3) / 4, cus), true, false};
 }
 
 }  // namespace
@@ -900,12 +918,12 @@ hipError_t launch_rnn_prep(const double* W, uint32_t n, void* out, int form, hip
   return hipGetLastError();
 }
 
-RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t runs, uint32_t cus) {
+RnnPlan plan_rnn(int precision, uint32_t n_units, uint64_t settings, uint64_t runs, uint32_t cus) {
   switch (n_units) {
-    case 64: return plan_nb<4>(precision, runs, cus);
-    case 128: return plan_nb<8>(precision, runs, cus);
-    case 192: return plan_nb<12>(precision, runs, cus);
-    default: return plan_nb<16>(precision, runs, cus);
+    case 64: return plan_nb<4>(precision, settings, runs, cus);
+    case 128: return plan_nb<8>(precision, settings, runs, cus);
+    case 192: return plan_nb<12>(precision, settings, runs, cus);
+    default: return plan_nb<16>(precision, settings, runs, cus);
   }
 }
 

@@ -2,6 +2,9 @@
 // code with a handle of 256 compute units and 160 KB of LDS.
 //   plan_check {launch|queue} kind precision settings trials max_steps n_bins every
 // -> chunk, workgroups, lanes of a draining team, direct counting (0 or 1), scan form (0 or 1)
+// or of a rate network:
+//   plan_check rnn units precision settings trials 0 0 0
+// -> form, workgroups, 0, direct counting, runs dealt out in turn (0 or 1)
 #include <cstdlib>
 
 #include "../../paper_2110_15425_amd/csrc/api.hip"
@@ -13,6 +16,12 @@ int main(int argc, char** argv) {
   h.cu_count = 256;
   h.lds_per_block = 163840;
   const uint32_t kind = atoi(argv[2]), prec = atoi(argv[3]);
+  if (argv[1][0] == 'r') {
+    const uint64_t S = strtoull(argv[4], nullptr, 10), T = strtoull(argv[5], nullptr, 10);
+    const cm::RnnPlan p = cm::plan_rnn(prec, kind, S, S * T, 256);
+    printf("%d %u 0 %d %d\n", p.form, p.groups, p.direct ? 1 : 0, p.dealt ? 1 : 0);
+    return 0;
+  }
   h.tune[kind][prec] = default_tuning(kind, prec);
   double params[16] = {0.1, 0.5, 1.0, 0.1, 0.8};
   cm_model m{};

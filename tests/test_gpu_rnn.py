@@ -188,3 +188,27 @@ def test_rnn_fp64_companions(n_units, settings):
     a, b = (cm.run(W.rnn(gains=g, **kw), dumps=True)["run_state"].reshape(settings, 4, -1) for g in (tame, wild))
     assert np.abs(b[1::2, :, 2:]).max() > 700 and np.abs(b[::2, :, 2:]).max() < 80
     assert np.array_equal(a[::2], b[::2])
+
+
+@pytest.mark.parametrize("n_units,settings,trials,n_bins", [
+    (192, 3, 10_923, 60), (256, 17, 2000, 100), (256, 19, 1800, 100),  # 64 runs each and more; the widest window
+    (256, 20, 1700, 100), (192, 1000, 33, 40), (256, 33_000, 1, 60),  # in global memory
+    (256, 2, 16_400, 60), (192, 3, 10_922, 60), (256, 3, 1, 40),  # consecutive
+])
+def test_rnn_bf16_dealt_runs(n_units, settings, trials, n_bins):
+    """Runs dealt out to the workgroups in turn: every run is there once, counted as its
+    own outputs say, and the same whatever other settings it is dealt out with."""
+    from parity import reduce_dumps
+    gains = np.geomspace(0.02, 30.0, settings)
+    kw = dict(n_units=n_units, trials=trials, seed=51, max_steps=max(n_bins, 60), n_bins=n_bins, thresh=0.2,
+              precision=W.BF16_PROJ)
+    print(f"rnn dealt {n_units} units {settings} x {trials}", flush=True)
+    w = W.rnn(gains=gains, **kw)
+    g = cm.run(w, dumps=True)
+    h, s = reduce_dumps(w, g, [-1] * settings)
+    assert np.array_equal(h, g["hist"]) and np.array_equal(s, g["stats"])
+    assert int(g["stats"][:, :3].sum()) == settings * trials
+    part = cm.run(W.rnn(gains=gains[:2], **kw), dumps=True)
+    n = min(settings, 2) * trials
+    for k in ("run_choice", "run_step", "run_flag", "run_state"):
+        assert np.array_equal(part[k], g[k][:n]), k

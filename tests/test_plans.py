@@ -70,3 +70,12 @@ def test_scan_chunks(plan, settings, trials, chunk, prec):
     """Runs of a scan workgroup of eight wavefronts: five to four times sqrt(runs / 600)."""
     p = plan("launch", W.DDM, prec, settings, trials)
     assert p["scan"] and p["chunk"] == chunk
+
+
+@pytest.mark.parametrize("units,prec,settings,trials,dealt", [
+    (256, W.BF16_PROJ, 16, 4096, True), (192, W.BF16_PROJ, 3, 10_923, True), (192, W.BF16_PROJ, 3, 10_922, False),
+    (256, W.BF16_PROJ, 1, 65_536, False), (256, W.BF16_PROJ, 2, 32_768, False), (256, W.BF16_PROJ, 3, 1, False),
+    (128, W.BF16_PROJ, 16, 4096, False), (64, W.BF16_PROJ, 16, 4096, False), (256, W.FP64, 16, 4096, False)])
+def test_rate_networks_that_deal_runs_out(plan, units, prec, settings, trials, dealt):
+    """Where all workgroups are resident at once, two on a CU, and settings may differ in length."""
+    assert plan("rnn", units, prec, settings, trials)["scan"] == dealt
