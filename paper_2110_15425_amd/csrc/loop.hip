@@ -493,6 +493,13 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
     // with its reciprocal, which saves a division per allocation and step
     const bool pow2 = (M & (M - 1u)) == 0u;
     const double inv_m = 1.0 / (double)M;
+    // A team of up to 16 lanes covers the allocations: each lane's own stays with it.  (Read
+    // anew each step from the [9][J] table, small FP32 launches, bound by their longest run,
+    // were up to 5 % slower than with a table by allocation; kept, 7 % faster: 100 x 10 runs, L
+    // = 2, M = 4, 137 / 142 / 129 us by allocation, anew and kept, 1,000 x 1, L = 4, 181 / 191 / 171.)
+    const uint32_t own = min(j0, J - 1u);
+    const Drive<PREC> own_in = drive[own];
+    const double own_cost = kappa * a.norm2[own];
     double x0 = 0.0, x1 = 0.0;
     bool flag = false;
     int choice = -1;
@@ -516,7 +523,7 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
           ju[u] = j + u * P < J ? j + u * P : j;
-          in[u] = drive[ju[u]];
+          in[u] = P < 64 ? own_in : drive[ju[u]];
           gs[u] = 0.0;
         }
         for (uint32_t m = 0; m < M; ++m) {
@@ -541,7 +548,7 @@ __global__ __launch_bounds__(kLoopBlock) void loop_kernel(LoopArgs a) {
             asm volatile("" ::: "memory");
             mean = gs[u] / (double)M;
           }
-          const double V = kappa * a.norm2[jj] - mean;
+          const double V = (P < 64 ? own_cost : kappa * a.norm2[jj]) - mean;
           if (V < bv) {
             sv = bv;
             bv = V;
