@@ -65,14 +65,20 @@ BATCH = 12
 # valid only for the kernel sources it was measured on, and given per
 # runs-per-lane (the number of workgroup flushes, hence the write traffic,
 # depends on it).
-TRAFFIC = {"sources_sha256": "92aedc09db501b224c29307fc0f817414728982c8015ef1d95e484a77932324c",
+TRAFFIC = {"sources_sha256": "f960bf133fa7af0addc9bba4f647898ff12d4f0cfda24f6d4615334528fe341d",
            "batch": 12,
-           # profiles/sim_lane_lca_fp32_conflict_batched.md; key "runs_per_lane,block,tail_sweeps"
-           "bytes_per_launch": {"4,256,0": 6362976, "6,256,0": 5474848, "8,256,0": 4985344, "4,256,2": 6780704,
-                                "4,256,4": 7199760, "6,256,2": 5765248, "6,256,4": 6055616, "8,256,2": 5214944,
-                                "8,256,4": 5444768, "4,512,0": 4987392, "6,512,0": 4443936, "8,512,0": 4047104,
-                                "4,512,2": 5216992, "4,512,4": 5446816, "6,512,2": 4615888, "6,512,4": 4788416,
-                                "8,512,2": 4204000, "8,512,4": 4361248}}
+           # profiles/sim_lane_lca_fp32_conflict_batched.md; key "runs_per_lane,block,tail_sweeps".
+           # The build capped for eight wavefronts per SIMD spills a register (2 MB a launch).
+           "bytes_per_launch": {"4,256,0": 6352736, "4,256,2": 6770464, "4,256,4": 7189552, "6,256,0": 5464576,
+                                "6,256,2": 5755008, "6,256,4": 6045376, "8,256,0": 4975104, "8,256,2": 5204704,
+                                "8,256,4": 5434528, "4,512,0": 4976128, "4,512,2": 5205728, "4,512,4": 5435552,
+                                "6,512,0": 4432672, "6,512,2": 4604608, "6,512,4": 4777152, "8,512,0": 4035840,
+                                "8,512,2": 4192736, "8,512,4": 4349984},
+           "bytes_per_launch_uncapped": {"4,256,0": 4263904, "4,256,2": 4681632, "4,256,4": 5100672, "6,256,0": 3375744,
+                                         "6,256,2": 3666208, "6,256,4": 3956544, "8,256,0": 2886384, "8,256,2": 3115936,
+                                         "8,256,4": 3345792, "4,512,0": 2878848, "4,512,2": 3108448, "4,512,4": 3338272,
+                                         "6,512,0": 2335392, "6,512,2": 2507328, "6,512,4": 2679872, "8,512,0": 1938560,
+                                         "8,512,2": 2095456, "8,512,4": 2252704}}
 KERNEL_SOURCES = ("paper_2110_15425_amd/csrc/sim_lane.hip", "paper_2110_15425_amd/csrc/rng.hpp",
                   "paper_2110_15425_amd/csrc/normal64.hpp", "paper_2110_15425_amd/csrc/lca_step.hpp",
                   "paper_2110_15425_amd/csrc/window.hpp", "paper_2110_15425_amd/csrc/internal.hpp",
@@ -442,7 +448,8 @@ def main():
     kern_rate = head["run_steps"] / (head["kern_ms"] / 1e3)
     traffic = None
     if TRAFFIC["sources_sha256"] == sources_hash() and TRAFFIC["batch"] == BATCH:
-        traffic = TRAFFIC["bytes_per_launch"].get(
+        capped = tuned.get("waves_per_simd", 0) == 8
+        traffic = TRAFFIC["bytes_per_launch" if capped else "bytes_per_launch_uncapped"].get(
             f"{tuned['runs_per_lane']},{tuned['block']},{tuned.get('tail_sweeps', 0)}")
     line = {
         "metric": "run-timesteps/sec on 1 MI355X (FP32 batched vs FP64 plain)",
