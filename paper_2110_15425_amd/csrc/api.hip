@@ -563,8 +563,15 @@ cm_status plan_lane(cm_handle* h, const cm_model* m, const cm_sweep* s, const cm
       // 1 / 2 / 3 runs per lane: FP64 218 / 199 / 221 us, FP32 141 / 133 / 144;
       // drift-diffusion of 10^6 runs, FP64, 2 / 3 / 4: 345 / 338 / 331; 10^7
       // runs FP64, 4 / 6 / 8: 2115 / 2077 / 2106.
+      // A conflict network keeps two runs per lane where the GPU would hold three or
+      // four, since a larger chunk of short runs leaves more lanes idle at its end: 10^6
+      // runs, 2 / 3 / 4, control 0 (some 25 steps) FP64 149 / 164 / 154, FP32 94 / 102;
+      // control 5 (some 80) 274 / 295 / 278 and 172 / 183; time course FP32 of 64
+      // settings, 1.2 x 10^6 runs, short 139 / 150, long 256 / 247.  A launch that just
+      // fits three loses up to 5 % (1.37 x 10^6 FP32 220 / 209).
       rpl = (launch_runs + once - 1) / once;
       if (rpl > 4) rpl = std::max<uint64_t>(3, std::min<uint64_t>(8, launch_runs / (4096ull * cus)));
+      else if (m->kind == CM_CONFLICT_LCA) rpl = std::min<uint64_t>(rpl, 2);
       chunk = (uint64_t)block * rpl;
     }
   }

@@ -63,6 +63,17 @@ def test_ddm_forms(plan, settings, trials, scan, prec):
     assert plan("launch", W.DDM, prec, settings, trials)["scan"] == scan
 
 
+@pytest.mark.parametrize("every", [0, 10])
+@pytest.mark.parametrize("kind,prec,runs,per_lane", [
+    (W.LCA, W.FP64, 640_000, 2), (W.LCA, W.FP64, 655_361, 2), (W.LCA, W.FP64, 1_310_720, 2), (W.LCA, W.FP64, 1_310_721, 3),
+    (W.LCA, W.FP32_STEP, 458_753, 2), (W.LCA, W.FP32_STEP, 1_000_000, 2), (W.LCA, W.FP32_STEP, 1_835_008, 2),
+    (W.LCA, W.FP32_STEP, 1_835_009, 3), (W.DDM, W.FP64, 1_000_000, 3), (W.DDM, W.FP32_STEP, 1_000_000, 3)])
+def test_runs_per_lane(plan, kind, prec, runs, per_lane, every):
+    """Conflict networks stay at two runs per lane while the GPU would hold up to four."""
+    p = plan("launch", kind, prec, 1, runs, every=every)
+    assert not p["scan"] and not p["direct"] and p["chunk"] == 256 * per_lane
+
+
 @pytest.mark.parametrize("prec", [W.FP64, W.FP32_STEP])
 @pytest.mark.parametrize("settings,trials,chunk", [(1, 1000, 8), (1, 5000, 16), (1, 10_000, 24), (1, 20_000, 32),
                                                    (1, 30_000, 32), (1, 32_768, 32), (10, 1000, 16), (10, 2000, 24)])
